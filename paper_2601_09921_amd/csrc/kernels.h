@@ -92,8 +92,16 @@ struct F32Params {
     SyndromeIn in;          // in.N: stabilizers (bits per measurement round)
     int ntok;               // tokens per window
     const int* tok_stab;    // [ntok] stabilizer of each token or -1; null: token s = stabilizer s
-    const float* w;         // blob tensors in blob order (fp32)
+    // weights, each matrix as [column group of D][k / 4][D columns][4]: per layer Wq Wk Wv Wo W1 W2
+    const float* stream;
+    const float* vecs;      // [L][9 D + F]: b_q b_k b_v b_o g1 be1 b2 g2 be2 b1
+    const float* we;        // [D]
     const float* S0;        // b_e + PE per token [ntok][D]
+    const float* wc;        // readout convolution, k = tap * D + in
+    const float* bc;        // [D]
+    const float* wo;        // [d][D]
+    float bo;
+    float beta[3];
     const int* cell_token;  // [(d+1)*(d+1)]
     float* logits;          // logits[win * readouts + k] after round W - readouts + k
     uint8_t* bits;
@@ -101,10 +109,11 @@ struct F32Params {
     int D, L, H, F;
     const int* emb_nb;      // embedder residual block as in TokParams, or null
     const float* emb_tab;
-    const float* conv_w;    // dilated convolutions: per layer Wd[3][3][3][D][D] bd[3][D], or null
+    const float* conv_w;    // dilated convolutions: per layer and unit W (k = tap * D + in), b[D]; or null
     int dil[3];             // their dilations (grid token set: token = cell)
     int readouts;           // readouts after the last `readouts` rounds (1: final state only)
     float kappa, eps;
+    float scale;            // 1 / sqrt(head size)
 };
 
 // The state-resident decoder (resident.hip): every round and layer of a batch of windows in

@@ -273,6 +273,18 @@ void append_resident_stream(std::vector<uint16_t>& out, const float* Wq, const f
     }
 }
 
+// The fp32 kernel's layout of W [K][O] row-major (y = x W): [O / D][K / 4][D][4], i.e. per column
+// group of D, the D columns' runs of four consecutive k.
+void append_f32(std::vector<float>& out, const float* W, int K, int O, int D) {
+    const size_t at = out.size();
+    out.resize(at + (size_t)K * O);
+    float* dst = out.data() + at;
+    for (int cg = 0; cg < O / D; ++cg)
+        for (int k4 = 0; k4 < K / 4; ++k4)
+            for (int c = 0; c < D; ++c, dst += 4)
+                for (int i = 0; i < 4; ++i) dst[i] = W[(size_t)(4 * k4 + i) * O + cg * D + c];
+}
+
 size_t layer_floats(int D, int F) { return (size_t)4 * D * D + 2 * (size_t)D * F + F + 9 * (size_t)D; }
 
 bool has_conv(const pwd_model_dims* m) {
@@ -388,7 +400,6 @@ struct pwd_decoder {
     uint16_t* Y = nullptr;
     uint16_t* G[2] = {nullptr, nullptr};   // dilated convolutions: bf16 token-major unit inputs
     int dil[3] = {0, 0, 0};        // their dilations (0: none)
-    size_t conv_off = 0;           // fp32 path: float offset of their tensors in the blob
     int* err = nullptr;
     void* static_scratch = nullptr;   // device address of `scratch` on this device
     // decode_stream scratch: the windows cut from a stream and their results
@@ -413,7 +424,8 @@ struct pwd_decoder {
     const int* cell_token = nullptr;
     const int* emb_nb = nullptr;   // embedder residual block (PWD_EMBED_RESNET): see emb_tables
     const float* emb_tab = nullptr;
-    const float* f32w = nullptr;   // fp32 path: the blob tensors as given
+    // fp32 path (F32Params)
+    const float *f32_stream = nullptr, *f32_vecs = nullptr, *f32_wc = nullptr, *f32_conv = nullptr;
     // the state-resident schedule (PWD_SCHEDULE_RESIDENT), when the configuration allows it
     bool resident_ok = false;
     int schedule = PWD_SCHEDULE_AUTO;
@@ -630,7 +642,8 @@ int decoder_create(const pwd_geometry* geom, const pwd_model_dims* dims, const v
 
     struct LayerOff { size_t post, qkv, post_vecs, bqkv, conv[3], conv_b[3]; };
     std::vector<LayerOff> loff(L);
-    size_t off_S0 = 0, off_we = 0, off_Wc = 0, off_bc = 0, off_wo = 0, off_f32 = 0, off_zero = 0;
+    size_t off_S0 = 0, off_we = 0, off_Wc = 0, off_bc = 0, off_wo = 0, off_zero = 0;
+    size_t off_f32_stream = 0, off_f32_vecs = 0, off_f32_wc = 0, off_f32_conv = 0;
     size_t off_res_stream = 0, off_res_vecs = 0;
     const bool resident_ok = dims->dtype == PWD_DTYPE_BF16 && !has_conv(dims) && dims->embedder == PWD_EMBED_LINEAR &&
                              resident_supported(D, (dec->ntok + 15) / 16, L, dims->mlp_ratio, D / H);
@@ -734,8 +747,33 @@ int decoder_create(const pwd_geometry* geom, const pwd_model_dims* dims, const v
             for (int f = 0; f < D; ++f) s0[(size_t)s * D + f] = (float)((double)b_e[f] + pe_row[f]);
         }
         off_S0 = put(s0.data(), s0.size() * 4);
-        off_f32 = put(w.data(), nf * 4);
-        dec->conv_off = nf - conv_floats(dims);
+        off_we = put(w.data(), (size_t)D * 4);
+        std::vector<float> st, vc, cv, rc;
+        for (int l = 0; l < L; ++l) {
+            const float* q = w.data() + 2 * D + (size_t)l * lf;
+            const float *Wq = q, *bq = Wq + D * D, *Wk = bq + D, *bk = Wk + D * D, *Wv = bk + D, *bv = Wv + D * D;
+            const float *Wo = bv + D, *bo = Wo + D * D, *g1 = bo + D, *be1 = g1 + D, *W1 = be1 + D;
+            const float *b1 = W1 + (size_t)D * F, *W2 = b1 + F, *b2 = W2 + (size_t)F * D, *g2 = b2 + D, *be2 = g2 + D;
+            for (const float* m : {Wq, Wk, Wv, Wo}) append_f32(st, m, D, D, D);
+            append_f32(st, W1, D, F, D);
+            append_f32(st, W2, F, D, D);
+            for (const float* v : {bq, bk, bv, bo, g1, be1, b2, g2, be2}) vc.insert(vc.end(), v, v + D);
+            vc.insert(vc.end(), b1, b1 + F);
+            if (has_conv(dims)) {
+                const float* cw = w.data() + nf - conv_floats(dims) + (size_t)l * (27 * (size_t)D * D + 3 * D);
+                for (int j = 0; j < 3; ++j) {
+                    append_f32(cv, cw + (size_t)j * 9 * D * D, 9 * D, D, D);
+                    cv.insert(cv.end(), cw + 27 * (size_t)D * D + j * D, cw + 27 * (size_t)D * D + (j + 1) * D);
+                }
+            }
+        }
+        append_f32(rc, tail, 4 * D, D, D);
+        off_f32_stream = put(st.data(), st.size() * 4);
+        off_f32_vecs = put(vc.data(), vc.size() * 4);
+        if (has_conv(dims)) off_f32_conv = put(cv.data(), cv.size() * 4);
+        off_f32_wc = put(rc.data(), rc.size() * 4);
+        off_bc = put(tail + 4 * (size_t)D * D, D * 4);
+        off_wo = put(tail + 4 * (size_t)D * D + D, (size_t)d * D * 4);
     }
     const float* bo_beta = tail + 4 * (size_t)D * D + D + (size_t)d * D;
     dec->bo_out = bo_beta[0];
@@ -807,7 +845,13 @@ int decoder_create(const pwd_geometry* geom, const pwd_model_dims* dims, const v
                     return cleanup_fail(fail(PWD_EHIP, "scratch clear: %s", hipGetErrorString(e)));
             }
     } else {
-        dec->f32w = fptr(off_f32);
+        dec->we = fptr(off_we);
+        dec->bc = fptr(off_bc);
+        dec->wo = fptr(off_wo);
+        dec->f32_stream = fptr(off_f32_stream);
+        dec->f32_vecs = fptr(off_f32_vecs);
+        dec->f32_wc = fptr(off_f32_wc);
+        if (has_conv(dims)) dec->f32_conv = fptr(off_f32_conv);
     }
     {
         const size_t mw = (size_t)dec->max_windows;
@@ -902,13 +946,20 @@ static int decode_impl(pwd_decoder* dec, const uint32_t* d_meas, const uint8_t* 
     if (dec->dtype == PWD_DTYPE_F32) {
         F32Params p;
         p.in = in;
-        p.w = dec->f32w;
+        p.stream = dec->f32_stream;
+        p.vecs = dec->f32_vecs;
+        p.we = dec->we;
         p.S0 = dec->S0;
+        p.wc = dec->f32_wc;
+        p.bc = dec->bc;
+        p.wo = dec->wo;
+        p.bo = dec->bo_out;
+        for (int i = 0; i < 3; ++i) p.beta[i] = dec->beta[i];
         p.ntok = dec->ntok;
         p.tok_stab = dec->tok_stab;
         p.emb_nb = dec->emb_nb;
         p.emb_tab = dec->emb_tab;
-        p.conv_w = dec->dil[0] ? dec->f32w + dec->conv_off : nullptr;
+        p.conv_w = dec->f32_conv;
         for (int j = 0; j < 3; ++j) p.dil[j] = dec->dil[j];
         p.cell_token = dec->cell_token;
         p.logits = d_logits;
@@ -917,6 +968,7 @@ static int decode_impl(pwd_decoder* dec, const uint32_t* d_meas, const uint8_t* 
         p.D = dec->D; p.L = dec->L; p.H = dec->H; p.F = dec->F;
         p.readouts = readouts;
         p.kappa = dec->kappa; p.eps = dec->eps;
+        p.scale = (float)(1.0 / std::sqrt((double)dec->dh));
         HIP_OK(timed(dec, PWD_STAGE_FP32_WINDOW, s, [&] { return launch_f32_window(p, s); }));
         return PWD_OK;
     }

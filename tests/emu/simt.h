@@ -294,6 +294,44 @@ inline emu_f32x4 emu_amdgcn_mfma_f32_16x16x16bf16_1k(emu_bf16x4 a, emu_bf16x4 b,
     return emu_mfma_16x16<emu_bf16x4, 4>(a, b, c);
 }
 
+// v_mfma_f32_16x16x4_f32: A row l % 16 and B column l % 16 at k = l / 16, one value per lane.
+inline emu_f32x4 emu_amdgcn_mfma_f32_16x16x4f32(float a, float b, emu_f32x4 c, int, int, int) {
+    struct AB { float a, b; };
+    emu::xput(AB{a, b}, 201);
+    emu::wave_sync();
+    const int lane = emu::g_cur->lane, col = lane & 15, g = lane >> 4;
+    emu_f32x4 d = c;
+    for (int i = 0; i < 4; ++i)
+        for (int k = 0; k < 4; ++k)
+            d[i] = std::fma(emu::xget<AB>(4 * g + i + 16 * k).a, emu::xget<AB>(col + 16 * k).b, d[i]);
+    emu::xdone();
+    return d;
+}
+// v_mfma_f32_4x4x1_16b_f32: block b = l / 4 holds A row l % 4 and B column l % 4; groups of 2^cbsz
+// blocks take the A rows of their block number `abid`. The lane's result rows are 0..3 of its
+// block's column l % 4.
+inline emu_f32x4 emu_amdgcn_mfma_f32_4x4x1f32(float a, float b, emu_f32x4 c, int cbsz, int abid, int) {
+    struct AB { float a, b; };
+    emu::xput(AB{a, b}, 202);
+    emu::wave_sync();
+    const int src = ((emu::g_cur->lane >> 2 >> cbsz) << cbsz) + abid;
+    emu_f32x4 d = c;
+    for (int i = 0; i < 4; ++i) d[i] = std::fma(emu::xget<AB>(4 * src + i).a, b, d[i]);
+    emu::xdone();
+    return d;
+}
+// v_mov_b32 with a lane permutation inside rows of 16, as far as the kernels use it: quad
+// permutations, half mirror (0x141) and mirror (0x140), every lane enabled.
+inline int emu_amdgcn_update_dpp(int, int src, int ctrl, int, int, bool) {
+    const int l = emu::g_cur->lane;
+    int from = l;
+    if (ctrl < 0x100) from = (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3);
+    else if (ctrl == 0x140) from = (l & ~15) | (15 - (l & 15));
+    else if (ctrl == 0x141) from = (l & ~7) | (7 - (l & 7));
+    else emu::report("update_dpp: control 0x%x is not emulated", ctrl);
+    return emu::exchange(src, from);
+}
+
 // ---- 8-bit floating point (MXFP8 path)
 typedef int emu_i32x8 __attribute__((ext_vector_type(8)));
 inline float emu_amdgcn_fmed3f(float a, float b, float c) { return std::fmax(std::fmin(a, b), std::fmin(std::fmax(a, b), c)); }
