@@ -9,7 +9,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpwdec.so")
-SOURCES = ["tok.hip", "attn.hip", "resident.hip", "readout.hip", "f32_window.hip", "stream.hip", "pwdec.cpp"]
+SOURCES = ["tok.hip", "wide.hip", "attn.hip", "resident.hip", "readout.hip", "f32_window.hip", "stream.hip", "pwdec.cpp"]
+# Sources compiled in parts side by side, one object per value of a macro (all of it without).
+PARTS = {"tok.hip": ("TOK_PART", 4), "wide.hip": ("WIDE_PART", 2)}
 # Per-source extra flags. The attention kernel keeps its MFMA accumulators in VGPRs (it needs
 # far fewer than 256), so no copies between accumulation and arithmetic registers; the token
 # kernel needs the AGPRs as accumulators.
@@ -21,6 +23,17 @@ HIPCC_FLAGS = [
     # no packed-fp32 VALU instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+
+def objects(objdir: str) -> list[tuple[str, str, list[str]]]:
+    """(source, object file, extra flags) of every compilation."""
+    out = []
+    for src in SOURCES:
+        macro, n = PARTS.get(src, ("", 1))
+        for i in range(n):
+            name, flags = (f"{src}.{i}.o", [f"-D{macro}={i}"]) if macro else (f"{src}.o", [])
+            out.append((src, os.path.join(objdir, name), EXTRA_FLAGS.get(src, []) + flags))
+    return out
 
 
 def hipcc() -> str:
@@ -50,11 +63,9 @@ def build(verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     objs, procs = [], []
-    for src in SOURCES:
-        obj = os.path.join(objdir, src + ".o")
+    for src, obj, extra in objects(objdir):
         objs.append(obj)
-        cmd = [hipcc(), *HIPCC_FLAGS, *EXTRA_FLAGS.get(src, []), "-x", "hip", "-c",
-               os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *HIPCC_FLAGS, *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append(_run(cmd, verbose))
     msgs = []
     for p in procs:
@@ -73,7 +84,7 @@ def build_host_asan(verbose: bool = False) -> str:
     kernels' objects of build() into _build/libpwdec_asan.so for the host checks in
     tests/asan. Builds the kernels' objects first if they are missing."""
     objdir = os.path.join(HERE, "_build")
-    kernels = [os.path.join(objdir, src + ".o") for src in SOURCES if src != "pwdec.cpp"]
+    kernels = [obj for src, obj, _ in objects(objdir) if src != "pwdec.cpp"]
     if not all(os.path.exists(o) for o in kernels):
         build(verbose)
     obj = os.path.join(objdir, "pwdec.cpp.asan.o")

@@ -27,6 +27,8 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace {
 
 #ifndef ATTN_WIDE
@@ -416,13 +418,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(At
     uint16_t* ks = reinterpret_cast<uint16_t*>(smem);   // [nbw][NF][512]: K fragments
     uint16_t* vs = ks + (size_t)nbw * NF * 512;          // [nbw + 1][NF][512]: V tiles, + a zero block
     constexpr int HPI = heads_per_item<DH>();
-    AttnItem it = make_item<DH>(p, sh, blockIdx.x * HPI);   // the pair's first head
+    const int item = blockIdx.x / p.parts, part = blockIdx.x - item * p.parts;
+    AttnItem it = make_item<DH>(p, sh, item * HPI);   // the pair's first head
     it.ks = ks;
     it.vs = vs;
 
-    // Each wavefront owns a contiguous share of the query blocks; Q of its first pass is
+    // Each wavefront owns a contiguous share of the item's query blocks; Q of its first pass is
     // loaded before the K/V staging, so its latency overlaps the staging.
-    const int qbeg = wave * nbw / WAVES, qend = (wave + 1) * nbw / WAVES;
+    const int share = part * WAVES + wave, shares = p.parts * WAVES;
+    const int qbeg = share * nbw / shares, qend = (share + 1) * nbw / shares;
     u16x8 qnext[QM][NF];
     if (qbeg < qend) load_q<NF, QM>(sh, it.q0, qbeg, qend, lane, qnext);
 
@@ -446,12 +450,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(At
 }
 
 template <int DH, int WAVES>
-hipError_t launch_shape(const AttnParams& p, int nwin, hipStream_t s) {
+hipError_t launch_shape(AttnParams p, int nwin, int parts, hipStream_t s) {
+    p.parts = parts;
     const size_t smem = attn_smem_bytes(DH, p.Npad, p.nbw);
     hipError_t e = hipFuncSetAttribute((const void*)attn_kernel<DH, WAVES>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    attn_kernel<DH, WAVES><<<dim3((unsigned)nwin * p.H / heads_per_item<DH>()), dim3(WAVES * 64), smem, s>>>(p);
+    attn_kernel<DH, WAVES><<<dim3((unsigned)nwin * p.H / heads_per_item<DH>() * parts), dim3(WAVES * 64), smem, s>>>(p);
     return hipGetLastError();
 }
 
@@ -469,11 +474,20 @@ hipError_t launch_dh(const AttnParams& p, int nwin, hipStream_t s) {
     constexpr int QM = Frag<DH>::QMAX;
     const size_t tile = attn_smem_bytes(DH, p.Npad, p.nbw);
     const int fit = (int)(160 * 1024 / tile);
-    if (p.nbw <= QM) return launch_shape<DH, 1>(p, nwin, s);
-    if (QM >= 4 && fit >= 8) return launch_shape<DH, 1>(p, nwin, s);
-    if (QM >= 4 ? fit >= 4 : p.nbw <= 2 * QM) return launch_shape<DH, 2>(p, nwin, s);
-    if (ATTN_WIDE && tile > 80 * 1024) return launch_shape<DH, 8>(p, nwin, s);
-    return launch_shape<DH, 4>(p, nwin, s);
+    // Few items: the query blocks of an item in several workgroups (each stages the item's K and V
+    // again) of four wavefronts, eight where a tile fills a CU, until every CU has as many
+    // workgroups as it keeps (two; one) or a wavefront has a single block. d25, 64 items: 11.5
+    // against 19.4 us in one workgroup per item; 120 tokens, 224 items: 7.1 against 9.4. From half
+    // as many items on, one workgroup per item is as fast (d25, 416 items: 38.0 against 37.8).
+    const int items = nwin * p.H / heads_per_item<DH>();
+    const int waves = fit < 2 ? 8 : 4, parts = std::min(256 * std::min(fit, 2) / items, p.nbw / waves);
+    if (parts >= 2)
+        return waves == 8 ? launch_shape<DH, 8>(p, nwin, parts, s) : launch_shape<DH, 4>(p, nwin, parts, s);
+    if (p.nbw <= QM) return launch_shape<DH, 1>(p, nwin, 1, s);
+    if (QM >= 4 && fit >= 8) return launch_shape<DH, 1>(p, nwin, 1, s);
+    if (QM >= 4 ? fit >= 4 : p.nbw <= 2 * QM) return launch_shape<DH, 2>(p, nwin, 1, s);
+    if (ATTN_WIDE && tile > 80 * 1024) return launch_shape<DH, 8>(p, nwin, 1, s);
+    return launch_shape<DH, 4>(p, nwin, 1, s);
 }
 
 }  // namespace

@@ -63,6 +63,7 @@ struct AttnParams {
     const uint16_t* QKV;
     uint16_t* Y;
     int N, Npad, nbw, H;    // Q arrives pre-scaled by log2(e)/sqrt(dh)
+    int parts;              // workgroups per item (set by the launcher)
 };
 
 struct ReadoutParams {
@@ -143,6 +144,7 @@ int tok_bv_rep(int D, int F);
 int tok_mx_qkv_frags();     // MXFP8 fragments per Q/K/V chunk
 int tok_mx_scale_slot();    // 1 KB slot of a chunk that holds its MXFP8 weight scales
 hipError_t launch_tok(int D, int F, int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
+hipError_t launch_wide(int D, int F, int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
 hipError_t launch_conv(int D, bool gout, const ConvParams& p, int64_t n_tb, hipStream_t s);
 hipError_t launch_attn(int dh, const AttnParams& p, int nwin, hipStream_t s);
 hipError_t launch_readout(const ReadoutParams& p, hipStream_t s);

@@ -76,36 +76,49 @@ PWD_DEV void sched_pipeline_pairs() {
     __builtin_amdgcn_sched_group_barrier(0x008, TAIL, 0);
 }
 
-// LayerNorm over the D features of each token (biased variance, two passes); gamma and
-// beta are in LDS.
+// LayerNorm statistics of a token block held as C fragments (biased variance, two passes), and
+// their application to one value.
+template <int RT>
+PWD_DEV void ln_stats(const f32x4 (&x)[RT], float eps, float& mean, float& rstd) {
+    constexpr float inv_d = 1.0f / (RT * 16);
+    float s = 0.f;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) s += (x[rt][0] + x[rt][1]) + (x[rt][2] + x[rt][3]);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    mean = s * inv_d;
+    float v = 0.f;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float c = x[rt][i] - mean;
+            v += c * c;
+        }
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    rstd = rsqrtf(v * inv_d + eps);
+}
+PWD_DEV float ln_apply(float x, float mean, float rstd, float gamma, float beta) {
+    return (x - mean) * rstd * gamma + beta;
+}
+
+// LayerNorm over the D features of each token held as C fragments; gamma and beta are in LDS.
 template <int RT, int TB>
 PWD_DEV void layer_norm(f32x4 (&x)[RT][TB], const float* gamma, const float* beta, float eps, int g) {
-    constexpr float inv_d = 1.0f / (RT * 16);
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
-        float s = 0.f;
+        f32x4 y[RT];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) s += (x[rt][b][0] + x[rt][b][1]) + (x[rt][b][2] + x[rt][b][3]);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        const float mean = s * inv_d;
-        float v = 0.f;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float c = x[rt][b][i] - mean;
-                v += c * c;
-            }
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        const float rstd = rsqrtf(v * inv_d + eps);
+        for (int rt = 0; rt < RT; ++rt) y[rt] = x[rt][b];
+        float mean, rstd;
+        ln_stats<RT>(y, eps, mean, rstd);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const f32x4 gm = ld4(gamma + rt * 16 + 4 * g);
             const f32x4 bt = ld4(beta + rt * 16 + 4 * g);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[rt][b][i] = (x[rt][b][i] - mean) * rstd * gm[i] + bt[i];
+            for (int i = 0; i < 4; ++i) x[rt][b][i] = ln_apply(x[rt][b][i], mean, rstd, gm[i], bt[i]);
         }
     }
 }

@@ -44,13 +44,17 @@
 #include "common.h"
 #include "kernels.h"
 #include "pipeline.h"
+#include "tokshape.h"
 
 #include <type_traits>
 #include <utility>
 
-namespace {
+hipError_t launch_tok_256_4(int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
+hipError_t launch_tok_256_5(int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
+hipError_t launch_tok_128_4(int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
+hipError_t launch_tok_128_5(int flags, const TokParams& p, int64_t n_tb, hipStream_t s);
 
-constexpr int FRAG = 512;       // bf16 values per fragment (1 KB)
+namespace {
 
 // Two 16-token blocks per wavefront and 4 wavefronts per workgroup, within 256 registers and
 // 80 KB of LDS so that two workgroups share a CU: each SIMD runs two wavefronts, and one
@@ -59,40 +63,6 @@ constexpr int FRAG = 512;       // bf16 values per fragment (1 KB)
 template <int D, int FLAGS>
 constexpr int tok_waves() { return 4; }
 constexpr int TB = 2;
-
-template <int D, int NW, int MR>
-struct Shape {
-    static constexpr int CHUNK = 32;                  // weight fragments per LDS chunk
-    static constexpr int RT = D / 16;                 // 16-row C tiles of a D-vector
-    static constexpr int KS = D / 32;                 // 32-deep k-steps of a D-vector
-    static constexpr int F = MR * D;                  // feed-forward width (MR = 4 or 5)
-    static constexpr int CH = 8192 / D;               // hidden units per feed-forward chunk
-    static constexpr int NMLP = F / CH;               // feed-forward sub-chunks (32 fragments each)
-    static constexpr int MLP_PER = CHUNK / 32;        // feed-forward sub-chunks per LDS chunk
-    static constexpr int MLP_CHUNKS = NMLP / MLP_PER;
-    static constexpr int WO_CHUNKS = RT * KS / CHUNK;
-    static constexpr int QKV_CHUNKS = (3 * D / 16) * KS / CHUNK;
-    static constexpr int OG_PER_CHUNK = CHUNK / (2 * KS);
-    static constexpr int POST_CHUNKS = WO_CHUNKS + MLP_CHUNKS;
-    static_assert((CH / 16) * KS + RT * (CH / 32) == 32, "32 fragments per feed-forward sub-chunk");
-    // MXFP8 (TOK_MX): 8-bit fragments of 16 rows x 128 k (2 KB, two 1 KB halves = two reads).
-    // A feed-forward chunk holds the CH hidden units' W1 fragments (hidden row tile, k-step)
-    // followed by their bf16 W2 fragments, a Q/K/V chunk 12 fragments (output group, k-step,
-    // row tile); slot MX_SCALE_SLOT holds the chunk's weight scales, lane-major, byte j of a
-    // lane for 8-bit fragment j; the other slots are unused.
-    static constexpr int KS8 = D / 128;
-    static constexpr int MX_SCALE_SLOT = 24;
-    static constexpr int MX_NW1 = (CH / 16) * KS8;
-    static constexpr int MX_FFN_READS = 2 * MX_NW1 + RT * (CH / 32);
-    static constexpr int MX_QKV_FRAGS = 12;
-    static constexpr int MX_OPC = MX_QKV_FRAGS / (2 * KS8);   // output groups per Q/K/V chunk
-    static constexpr int MX_QKV_READS = 2 * MX_QKV_FRAGS;
-    static constexpr int MX_QKV_CHUNKS = (3 * D / 32) / MX_OPC;
-    static_assert(MX_FFN_READS == MX_SCALE_SLOT && MX_QKV_READS == MX_SCALE_SLOT, "data ahead of the scales");
-    static_assert((3 * D / 32) % MX_OPC == 0 && MX_NW1 <= 4 && MLP_PER == 1, "MXFP8 chunk layout");
-    static_assert(NMLP % MLP_PER == 0, "whole feed-forward chunks");
-    static_assert(RT * KS % CHUNK == 0 && (3 * D / 16) * KS % CHUNK == 0, "whole chunks");
-};
 
 #ifndef TOK_NT
 #define TOK_NT 1
@@ -130,20 +100,6 @@ PWD_DEV void stfrag(uint16_t* __restrict__ base, int64_t frag, int lane, bf16x8 
     st_stream(reinterpret_cast<u16x8*>(base + (frag * 64 + lane) * 8), __builtin_bit_cast(u16x8, v));
 }
 
-
-PWD_DEV u16x4 to_bf16x4(f32x4 v) {
-    u16x4 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = __builtin_bit_cast(uint16_t, (__bf16)v[i]);
-    return r;
-}
-
-PWD_DEV f32x4 relu4(f32x4 v) {
-    f32x4 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = v[i] > 0.f ? v[i] : 0.f;
-    return r;
-}
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -325,23 +281,6 @@ struct WeightPipe {
     }
 };
 
-// LDS of one workgroup (two per CU): the weight ring (two 32-fragment buffers) + vectors.
-constexpr int LDS_BUDGET = 80 * 1024, RING_BYTES = 2 * 32 * FRAG * 2;
-
-// b_v is stored with each value four times (the bias of a V tile is one column value per
-// lane, loaded as the f32x4 an accumulator starts from) where that fits in LDS, else once.
-constexpr int bv_rep(int D, int F) { return (12 * D + F) * 4 + RING_BYTES <= LDS_BUDGET ? 4 : 1; }
-
-// Per-launch vectors staged in LDS once: [bo g1 be1 b2 g2 be2 | b1 (F) | b_q b_k | b_v].
-template <int D, int F>
-struct Vecs {
-    static constexpr int BO = 0, G1 = D, BE1 = 2 * D, B2 = 3 * D, G2 = 4 * D, BE2 = 5 * D;
-    static constexpr int REP = bv_rep(D, F);
-    static constexpr int B1 = 6 * D, BQKV = 6 * D + F, BV = BQKV + 2 * D, QKV_VECS = (2 + REP) * D;
-    static constexpr int SIZE = BQKV + QKV_VECS;
-    static_assert(SIZE * 4 + RING_BYTES <= LDS_BUDGET, "vector table fits");
-};
-
 // Global stores a wavefront issues in one Q/K/V chunk after its last load of the next
 // chunk. Output group o2 is stored in the MFMA step of its last fragment read,
 // r = (o2 + 1) * 2 KS - 1, which follows the loads issued after reads up to r + LA - 1.
@@ -426,35 +365,7 @@ __global__ __launch_bounds__((tok_waves<D, FLAGS>() * 64), 2) void tok_kernel(To
     int row[TB];   // RESNET: the token's row of the block's table
     if constexpr ((FLAGS & TOK_EMBED) != 0) {
 #pragma unroll
-        for (int b = 0; b < TB; ++b) {
-            const int64_t tb = tb0 + b;
-            const int64_t w = tb / p.nbw;
-            const int s = (int)(tb - w * p.nbw) * 16 + col;   // token
-            ev[b] = 0.f;
-            row[b] = 0;
-            const int st = s < p.ntok ? (p.tok_stab ? p.tok_stab[s] : s) : -1;   // its stabilizer
-            if (w < p.in.nwin) {
-                const uint32_t* m = p.in.meas + w * (int64_t)(p.in.W + 1) * p.in.words;
-                const int type = p.in.types[w];
-                auto bit = [&](int q) -> uint32_t {   // event of stabilizer q in round t
-                    const uint32_t word = event_word(m, p.in.words, p.t, q >> 5, type, p.in.b_left, p.in.d);
-                    return (word >> (q & 31)) & 1u;
-                };
-                if (st >= 0) ev[b] = (float)bit(st);
-                if constexpr (RES) {
-                    if (s < p.ntok) {
-                        const int* nb = p.emb_nb + (size_t)s * 8;
-                        uint32_t pat = 0u;
-#pragma unroll
-                        for (int j = 0; j < 5; ++j) {
-                            const int q = nb[j];
-                            if (q >= 0) pat |= bit(q) << j;
-                        }
-                        row[b] = nb[5] * 32 + (int)pat;
-                    }
-                }
-            }
-        }
+        for (int b = 0; b < TB; ++b) token_event<RES>(p, tb0 + b, col, ev[b], row[b]);
     }
 
     // Per-launch vectors, staged in LDS by direct loads of 256 bytes (64 lanes x 4 bytes):
@@ -676,9 +587,7 @@ __global__ __launch_bounds__((tok_waves<D, FLAGS>() * 64), 2) void tok_kernel(To
                 if constexpr (RES) s0 += ld4(p.emb_tab + (size_t)row[b] * D + rt * 16 + 4 * g);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float emb = real ? e * we[i] + s0[i] : 0.f;
-                    const float prev = POST ? x[rt][b][i] : 0.f;
-                    x[rt][b][i] = p.kappa * (emb + prev);
+                    x[rt][b][i] = fold(real, e, we[i], s0[i], POST ? x[rt][b][i] : 0.f, p.kappa);
                 }
             }
         }
@@ -909,6 +818,24 @@ hipError_t launch_tok_d(int flags, const TokParams& p, int64_t n_tb, hipStream_t
     return hipGetLastError();
 }
 
+}  // namespace
+
+// The token kernel's variants are compiled in four parts (TOK_PART 0..3, one per d_model and
+// feed-forward ratio; all at once without it), so that a build can run them side by side.
+#if !defined(TOK_PART) || TOK_PART == 0
+hipError_t launch_tok_256_4(int flags, const TokParams& p, int64_t n_tb, hipStream_t s) { return launch_tok_d<256, 4>(flags, p, n_tb, s); }
+#endif
+#if !defined(TOK_PART) || TOK_PART == 1
+hipError_t launch_tok_256_5(int flags, const TokParams& p, int64_t n_tb, hipStream_t s) { return launch_tok_d<256, 5>(flags, p, n_tb, s); }
+#endif
+#if !defined(TOK_PART) || TOK_PART == 2
+hipError_t launch_tok_128_4(int flags, const TokParams& p, int64_t n_tb, hipStream_t s) { return launch_tok_d<128, 4>(flags, p, n_tb, s); }
+#endif
+#if !defined(TOK_PART) || TOK_PART == 3
+hipError_t launch_tok_128_5(int flags, const TokParams& p, int64_t n_tb, hipStream_t s) { return launch_tok_d<128, 5>(flags, p, n_tb, s); }
+
+namespace {
+
 // One residual unit of the dilated convolutions (model table: 3 x Conv2d(D, D) per layer;
 // App. A.2: the attention output scattered onto the 2-D grid), an implicit GEMM on MFMA:
 //   X[tok] += ReLU(b + sum_{a,e} W[a][e]^T G[cell(tok) + dil (a-1, e-1)])   (zero off the grid)
@@ -1107,9 +1034,15 @@ int tok_mx_scale_slot() { return Shape<256, 4, 4>::MX_SCALE_SLOT; }
 
 hipError_t launch_tok(int D, int F, int flags, const TokParams& p, int64_t n_tb, hipStream_t s) {
     if (n_tb <= 0) return hipSuccess;
-    if (D == 256 && F == 4 * D) return launch_tok_d<256, 4>(flags, p, n_tb, s);
-    if (D == 256 && F == 5 * D) return launch_tok_d<256, 5>(flags, p, n_tb, s);
-    if (D == 128 && F == 4 * D) return launch_tok_d<128, 4>(flags, p, n_tb, s);
-    if (D == 128 && F == 5 * D) return launch_tok_d<128, 5>(flags, p, n_tb, s);
+    // Few tokens: the feature-split kernel (bit-identical), where this one's 128-token workgroups
+    // would occupy few CUs. Post + QKV launch at d_model 256: 22 / 26 / 44 / 47 us for 78 / 507 / 780 /
+    // 1014 token blocks against 46 / 48 / 49 / 50 here; at 1560 85 against 54 (the weights are streamed
+    // once per two blocks there). At d_model 128, 688 blocks: 17 against 19 us; 1376: 23 against 20.
+    if (!(flags & TOK_MX) && n_tb <= 1024) return launch_wide(D, F, flags, p, n_tb, s);
+    if (D == 256 && F == 4 * D) return launch_tok_256_4(flags, p, n_tb, s);
+    if (D == 256 && F == 5 * D) return launch_tok_256_5(flags, p, n_tb, s);
+    if (D == 128 && F == 4 * D) return launch_tok_128_4(flags, p, n_tb, s);
+    if (D == 128 && F == 5 * D) return launch_tok_128_5(flags, p, n_tb, s);
     return hipErrorInvalidValue;
 }
+#endif
