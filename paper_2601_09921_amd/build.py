@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpwdec.so")
-SOURCES = ["tok.hip", "wide.hip", "attn.hip", "resident.hip", "readout.hip", "f32_window.hip", "stream.hip", "pwdec.cpp"]
+SOURCES = ["tok.hip", "wide.hip", "attn.hip", "resident.hip", "resident_split.hip", "readout.hip", "f32_window.hip", "stream.hip", "pwdec.cpp"]
 # Sources compiled in parts side by side, one object per value of a macro (all of it without).
 PARTS = {"tok.hip": ("TOK_PART", 4), "wide.hip": ("WIDE_PART", 2)}
 # Per-source extra flags. The attention kernel keeps its MFMA accumulators in VGPRs (it needs

@@ -136,6 +136,7 @@ struct ResidentParams {
 bool resident_supported(int D, int nbw, int L, int mr, int dh);
 int resident_chunk_fragments();
 hipError_t launch_resident(int mr, int dh, const ResidentParams& p, hipStream_t s);
+hipError_t launch_resident_split(int mr, int dh, const ResidentParams& p, hipStream_t s);
 
 hipError_t launch_events(const EventsParams& p, hipStream_t s);
 int64_t tok_block_granule();
