@@ -123,17 +123,18 @@ def sources(csrc: str = CSRC) -> list[str]:
 
 
 def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: str = INCLUDE, out: str = OUT,
-          lift: list[tuple[str, str]] = ()) -> str:
+          lift: list[tuple[str, str]] = (), base: str = "") -> str:
     """Translates and compiles every library source for the host; returns the library path.
     csrc / include / out default to the library's sources and tests/emu/_build. `lift`: extra
     (old, new) text substitutions, each of which must apply, e.g. to lift a configuration that
-    the library rejects so that a test can replay it on the CPU."""
+    the library rejects so that a test can replay it on the CPU. `base`: the folder of an
+    up-to-date build whose objects are taken for every source that no substitution changes."""
     src_out = os.path.join(out, "p", "csrc")
     inc_out = os.path.join(out, "include")
     os.makedirs(src_out, exist_ok=True)
     os.makedirs(inc_out, exist_ok=True)
     shutil.copy(os.path.join(include, "pwdec.h"), inc_out)
-    units, used = [], set()
+    units, used, lifted = [], set(), set()
     for f in sources(csrc):
         with open(os.path.join(csrc, f)) as fh:
             t = transform(fh.read())
@@ -141,6 +142,7 @@ def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: st
             if old in t:
                 t = t.replace(old, new)
                 used.add(old)
+                lifted.add(f)
         dst = os.path.join(src_out, f)
         with open(dst, "w") as fh:
             fh.write(t)
@@ -152,6 +154,9 @@ def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: st
     objs, procs = [], []
     for u in units + [os.path.join(HERE, "simt.cpp"), os.path.join(HERE, "units.cpp")]:
         obj = os.path.join(out, os.path.basename(u) + ".o")
+        if base and os.path.basename(u) not in lifted:
+            objs.append(os.path.join(base, os.path.basename(u) + ".o"))
+            continue
         cmd = [CLANG, *flags, "-c", u, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)

@@ -23,7 +23,8 @@ def waves(emu):  # noqa: F811
     out = os.path.join(build_emu.OUT, "waves")
     lib = os.path.join(out, "libpwdec_emu.so")
     if not os.path.exists(lib) or os.path.getmtime(lib) < os.path.getmtime(build_emu.LIB):
-        lib = build_emu.build(out=out, lift=[("SPLIT_MAX_WINDOWS = 512", "SPLIT_MAX_WINDOWS = 0")])
+        lib = build_emu.build(out=out, lift=[("SPLIT_MAX_WINDOWS = 512", "SPLIT_MAX_WINDOWS = 0")],
+                              base=build_emu.OUT)
     return run_emu.load(lib)
 
 
