@@ -193,7 +193,7 @@ def mxfp8_measurement(torch, pwdec, synth, names=("d7", "d11", "d25"), reps=3):
 # The sources each profiled stage's kernel is compiled from: its counter figures stay valid
 # while these files are unchanged, whatever happens to the other kernels.
 STAGE_SOURCES = {
-    "post_qkv": ("tok.hip", "common.h", "kernels.h", "pipeline.h"),
+    "post_qkv": ("tok.hip", "common.h", "kernels.h", "pipeline.h", "tokshape.h"),
     "attention": ("attn.hip", "common.h", "kernels.h"),
 }
 
