@@ -18,7 +18,7 @@
 // two phases to a layer ahead. Products split by k leave one partial sum per
 // wavefront in LDS, which the phase that reads them adds up.
 // Measured: d 3, d_model 64, 64 windows of 6 rounds 61 us; d 5, d_model 32, 1000 windows of 15
-// rounds 433 us (with FMA loops over LDS operands and one weight load per FMA: 636 and 5167 us).
+// rounds 437 us (with FMA loops over LDS operands and one weight load per FMA: 636 and 5167 us).
 // With the refills after a product instead of between its instructions, 66 us at d 3.
 //
 // Every output element is summed in a fixed order, so results do not depend on the batch.
@@ -58,7 +58,6 @@ struct F32Shape {
     static constexpr int R12 = cmax(R1 + R2, WAVES * PT * TQ * D);
     static constexpr int VEC = 9 * D + F;            // vectors of a layer
     static constexpr int RTAB = 4 * PT * TQ, CTAB = 27 * NP;   // gather tables (see the kernel)
-    static_assert(((KP - 1) * NP + NKB * 16) * S3 <= R12, "whole 16-key blocks are read");
     static constexpr size_t smem(int L, bool conv) {
         return sizeof(float) * ((size_t)NP * SX + R12 + WAVES + (size_t)L * VEC + RTAB + (conv ? CTAB : 0));
     }
@@ -110,7 +109,7 @@ PWD_DEV void refill(f32x4& w, const float* base, int off) {
 PWD_DEV void refill(f32x4&, std::nullptr_t, int) {}
 
 // Wavefronts per SIMD: at d_model 32 and up to 24 tokens four (128 registers, a few spilled) let
-// four workgroups share a CU: 433 against 477 us for the 1000 windows above with three.
+// four workgroups share a CU: 437 against 477 us for the 1000 windows above with three.
 template <int D, int MR, int NT>
 __global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT + MR <= 7 ? 4 : 3)) void f32_window_kernel(F32Params p) {
     using S = F32Shape<D, MR, NT>;
@@ -234,7 +233,8 @@ __global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT +
     };
 
     for (int i = tid; i < p.L * S::VEC; i += S::THREADS) vec[i] = p.vecs[i];
-    // token rows past N, which the products and the attention's whole 16-key blocks read, stay finite
+    // the state's rows past N, which the products read, stay zero: their results, in rows past N
+    // again, are never read as a token's
     for (int i = tid; i < NP * SX + S::R12; i += S::THREADS) X[i] = 0.f;
     for (int i = tid; i < S::RTAB; i += S::THREADS) {
         const int tap = i / (S::PT * TQ), pos = i % (S::PT * TQ);
@@ -351,15 +351,19 @@ __global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT +
     };
 
     // one (head, 16-query block): S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_16x16x4: a result
-    // register i of S^T (keys 4 g + i) is the operand of the product over those four keys
+    // register i of S^T (keys 4 g + i) is the operand of the product over those four keys. Keys from N
+    // on get score -inf and V = 0, so nothing that LDS holds there counts; rows from NP on (the last
+    // block's, where NP is no multiple of 16) belong to other values, which other wavefronts may be
+    // writing, and are not read: block row 0 stands in for them.
     auto attend = [&](int h, int qb) {
         const int lane = here(tid & 63), g = lane >> 4, c16 = lane & 15;
+        auto inside = [&](int kb, int r) { return (kb + 1) * 16 <= NP || kb * 16 + r < NP ? r : 0; };
         auto at = [&](int row, int cc) {   // Q, K or V element: its k partials
             float v = QP[row * S3 + cc];
             if constexpr (KP == 2) v += QP[(NP + row) * S3 + cc];
             return v;
         };
-        const int q = qb * 16 + c16;
+        const int q = qb * 16 + c16, qrow = NP % 16 == 0 || q < NP ? q : 0;
         f32x4 s[NKB];
         clear(s);
         // STEPS k-steps of four features from feature cc: their operands are read ahead of the products
@@ -368,9 +372,9 @@ __global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT +
             float a[STEPS][NKB], b[STEPS];
 #pragma unroll
             for (int k = 0; k < STEPS; ++k) {
-                b[k] = at(q, cc + 4 * k);
+                b[k] = at(qrow, cc + 4 * k);
 #pragma unroll
-                for (int kb = 0; kb < NKB; ++kb) a[k][kb] = at(kb * 16 + c16, D + cc + 4 * k);
+                for (int kb = 0; kb < NKB; ++kb) a[k][kb] = at(kb * 16 + inside(kb, c16), D + cc + 4 * k);
             }
 #pragma unroll
             for (int k = 0; k < STEPS; ++k)
@@ -405,7 +409,12 @@ __global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT +
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o = mfma16x16x4(at(kb * 16 + 4 * g + i, 2 * D + h * dh + row), s[kb][i], o);
+                for (int i = 0; i < 4; ++i) {
+                    // N > NP - TQ: only the last blocks can hold rows past it
+                    float v = at(kb * 16 + inside(kb, 4 * g) + i, 2 * D + h * dh + row);
+                    if ((kb + 1) * 16 > NP - TQ) v = kb * 16 + 4 * g + i < N ? v : 0.f;
+                    o = mfma16x16x4(v, s[kb][i], o);
+                }
             if (q < N && r0 + 4 * g < dh) *reinterpret_cast<f32x4*>(AO + q * SX + h * dh + r0 + 4 * g) = o * inv;
         }
     };

@@ -25,13 +25,25 @@ IDS = [f"d{s[0]}_D{s[3]}_H{s[5]}_r{s[6]}" + ("_grid" if s[7] else "") + ("_res" 
        ("_dil" if s[9] else "") + ("_rec" if s[10] else "") for s in SHAPES]
 
 
-def case(s):
-    """(workload, weights, measurement bits, types, oracle logits) of a shape."""
+# Token counts that end inside a block of 16 keys, every even hidden unit switched off by a bias of
+# -inf: a value that the network never uses, but that sits in LDS beside what it does use.
+OFF_SHAPES = [(3, 4, 2, 64, 2, 4, 4, False, False, (), False), (5, 5, 1, 64, 2, 1, 4, False, False, (), False),
+              (3, 4, 2, 32, 2, 4, 5, False, False, (), False), (5, 5, 2, 32, 2, 4, 4, False, False, (), True),
+              (5, 5, 1, 32, 2, 2, 4, True, False, (), False)]
+OFF_IDS = [f"d{s[0]}_D{s[3]}_H{s[5]}_r{s[6]}" + ("_grid" if s[7] else "") for s in OFF_SHAPES]
+
+
+def case(s, off=False):
+    """(workload, weights, measurement bits, types, oracle logits) of a shape; `off`: with every even
+    hidden unit of every layer switched off."""
     from oracle import decoder as O
     from paper_2601_09921_amd import synth
     d, W, B, D, L, H, r, grid, res, dil, rec = s
     wl = synth.Workload("x", d, W, B, 0.1, 0.0, D, L, H, r, synth.DTYPE_F32, grid=grid, resnet=res, dil=dil)
     w = synth.make_weights(wl, seed=3)
+    if off:
+        for lw in w["layers"]:
+            lw["b1"][::2] = -float("inf")
     meas, types = synth.make_windows(wl, seed=4, realistic_boundaries=False)
     o = (O.forward_windows_recurrent if rec else O.forward_windows)(meas, types, w, d, H, grid=grid)[0]
     return wl, w, meas, types, o

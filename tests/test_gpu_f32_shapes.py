@@ -3,17 +3,18 @@ larger batch equals the same window decoded alone."""
 import numpy as np
 import pytest
 
-from f32_shapes import IDS, SHAPES, case
+from f32_shapes import IDS, OFF_IDS, OFF_SHAPES, SHAPES, case
 from gpu_helpers import FP32_ATOL, FP32_RTOL, say, to_device
 from paper_2601_09921_amd import pwdec
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("s", SHAPES, ids=IDS)
-def test_matches_oracle(s):
+@pytest.mark.parametrize("s,off", [(s, False) for s in SHAPES] + [(s, True) for s in OFF_SHAPES],
+                         ids=IDS + [i + "_off" for i in OFF_IDS])
+def test_matches_oracle(s, off):
     import torch
-    wl, w, meas, types, o = case(s)
+    wl, w, meas, types, o = case(s, off)
     reps = 67   # a ragged batch, the shape's windows repeated
     dec = pwdec.Decoder.from_workload(wl, w, max_windows=reps)
     idx = np.arange(reps) % wl.B
