@@ -18,11 +18,15 @@ memory instruction reads that SGPR (the load address), or the load reads the reg
 value -- a load from the wrong address. Every direct load must therefore sit at least 5 wait
 states after the last vector write of its address registers on the straight-line path before it.
 """
+import functools
 import os
 import re
 import subprocess
+import tempfile
 
 import pytest
+
+from paper_2601_09921_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 OBJDIR = os.path.join(ROOT, "paper_2601_09921_amd", "_build")
@@ -37,15 +41,15 @@ FUNC = re.compile(r"^([0-9a-f]+) <(\w+)>:$")
 TARGET_RE = re.compile(r"<(\w+)\+0x([0-9a-f]+)>")
 
 
-def disassemble(obj: str, tmp) -> str:
-    fat = tmp / (os.path.basename(obj) + ".fatbin")
-    co = tmp / (os.path.basename(obj) + ".co")
-    subprocess.run([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", obj, str(tmp / "discard.o")],
-                   check=True, capture_output=True)
-    subprocess.run([f"{LLVM}/clang-offload-bundler", "--unbundle", "--type=o", f"--targets={TARGET}",
-                    f"--input={fat}", f"--output={co}"], check=True, capture_output=True)
-    return subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--mcpu=gfx950", str(co)], check=True,
-                          capture_output=True, text=True).stdout
+def disassemble(obj: str) -> str:
+    with tempfile.TemporaryDirectory() as tmp:
+        fat, co = os.path.join(tmp, "fatbin"), os.path.join(tmp, "co")
+        subprocess.run([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", obj, os.path.join(tmp, "discard.o")],
+                       check=True, capture_output=True)
+        subprocess.run([f"{LLVM}/clang-offload-bundler", "--unbundle", "--type=o", f"--targets={TARGET}",
+                        f"--input={fat}", f"--output={co}"], check=True, capture_output=True)
+        return subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--mcpu=gfx950", co], check=True,
+                              capture_output=True, text=True).stdout
 
 
 def functions(text: str):
@@ -144,31 +148,51 @@ def sgpr_hazards(insts, need_states: int = 5) -> list[str]:
     return problems
 
 
-def objects():
-    if not os.path.isdir(OBJDIR):
-        return []
-    return sorted(os.path.join(OBJDIR, f) for f in os.listdir(OBJDIR) if f.endswith(".hip.o"))
+# (source, object) of every compilation that holds kernels, as the build names them
+OBJECTS = [(src, obj) for src, obj, _ in build.objects(OBJDIR) if src.endswith(".hip")]
+IDS = [os.path.basename(obj) for _, obj in OBJECTS]
+# The kernels that stage through direct loads, and how many shapes of each (d_model and feed-forward
+# ratio; head size; d_model) the library has at least.
+STAGING = {"tok.hip": [("tok_kernel", 4), ("conv_kernel", 2)], "attn.hip": [("attn_kernel", 3)],
+           "resident.hip": [("resident_kernel", 4)]}
 
 
-@pytest.mark.parametrize("obj", objects(), ids=[os.path.basename(o) for o in objects()])
-def test_direct_lds_loads_complete_before_barriers(obj, tmp_path):
+@functools.lru_cache(maxsize=None)
+def kernels(obj):
+    """The functions of a built object; an object that the build lists and that is not there fails."""
     if not os.path.exists(f"{LLVM}/llvm-objdump"):
         pytest.skip("ROCm LLVM tools not found")
-    funcs = functions(disassemble(obj, tmp_path))
+    assert os.path.exists(obj), f"{obj} is missing: build the library"
+    funcs = functions(disassemble(obj))
     assert funcs, "no kernels found"
-    if os.path.basename(obj) in ("tok.hip.o", "attn.hip.o", "resident.hip.o"):   # these stage through direct loads
-        assert any(DMA.match(mn) for insts in funcs.values() for _, mn, _, _ in insts)
-    bad = {name: p for name, insts in funcs.items() if (p := check(insts))}
+    return funcs
+
+
+@pytest.mark.parametrize("src,obj", OBJECTS, ids=IDS)
+def test_direct_lds_loads_complete_before_barriers(src, obj):
+    bad = {name: p for name, insts in kernels(obj).items() if (p := check(insts))}
     assert not bad, bad
 
 
-@pytest.mark.parametrize("obj", objects(), ids=[os.path.basename(o) for o in objects()])
-def test_direct_lds_load_addresses_are_settled(obj, tmp_path):
-    if not os.path.exists(f"{LLVM}/llvm-objdump"):
-        pytest.skip("ROCm LLVM tools not found")
-    funcs = functions(disassemble(obj, tmp_path))
-    bad = {name: p for name, insts in funcs.items() if (p := sgpr_hazards(insts))}
+@pytest.mark.parametrize("src,obj", OBJECTS, ids=IDS)
+def test_direct_lds_load_addresses_are_settled(src, obj):
+    bad = {name: p for name, insts in kernels(obj).items() if (p := sgpr_hazards(insts))}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("src", sorted(STAGING))
+def test_every_staging_kernel_is_inspected(src):
+    """The objects above hold every kernel that stages through direct loads, with its direct loads: a
+    kernel or object that was renamed, split or left out is missed here, and an object file that the
+    build no longer writes is not looked at."""
+    for kernel, shapes in STAGING[src]:
+        found = {name: insts for s, obj in OBJECTS if s == src for name, insts in kernels(obj).items() if kernel in name}
+        assert len(found) >= shapes, (kernel, sorted(found))
+        without = [name for name, insts in found.items() if not any(DMA.match(mn) for _, mn, _, _ in insts)]
+        assert not without, without
+    if src == "tok.hip":   # one part per d_model and feed-forward ratio, each with its token kernels
+        for s, obj in OBJECTS:
+            assert s != src or any("tok_kernel" in name for name in kernels(obj)), obj
 
 
 def test_the_address_check_catches_a_fresh_sgpr():
