@@ -128,7 +128,8 @@ def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: st
     csrc / include / out default to the library's sources and tests/emu/_build. `lift`: extra
     (old, new) text substitutions, each of which must apply, e.g. to lift a configuration that
     the library rejects so that a test can replay it on the CPU. `base`: the folder of an
-    up-to-date build whose objects are taken for every source that no substitution changes."""
+    up-to-date build whose objects are taken for every source that no substitution changes (for
+    none where one changes a header)."""
     src_out = os.path.join(out, "p", "csrc")
     inc_out = os.path.join(out, "include")
     os.makedirs(src_out, exist_ok=True)
@@ -150,6 +151,8 @@ def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: st
             units.append(dst)
     if set(o for o, _ in lift) - used:
         raise ValueError(f"substitutions that matched nothing: {set(o for o, _ in lift) - used}")
+    if any(f.endswith(".h") for f in lifted):
+        base = ""
     flags = [opt, "-g", "-std=c++20", "-fPIC", "-w", "-I", HERE, "-I", src_out, "-x", "c++"]
     objs, procs = [], []
     for u in units + [os.path.join(HERE, "simt.cpp"), os.path.join(HERE, "units.cpp")]:

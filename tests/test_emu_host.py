@@ -187,3 +187,23 @@ def test_replay_of_the_recorded_gpu_fault(emu):
     o, _ = O.forward_windows(meas, types, w, 11, 8, grid=True)
     assert rc == 0 and emu.emu_errors() == 0
     assert np.abs(logits - o).max() <= BF16_ATOL
+
+
+def test_a_lifted_header_reaches_every_unit(tmp_path):
+    """A build on another's objects, with a substitution in a header: the units that include it are
+    compiled again."""
+    csrc = tmp_path / "csrc"
+    csrc.mkdir()
+    for f in ("kernels.h", "common.h"):
+        (csrc / f).write_text(open(os.path.join(build_emu.CSRC, f)).read())
+    (csrc / "shape.h").write_text("constexpr int LINE = 1;\n")
+    (csrc / "unit.hip").write_text(
+        '#include <hip/hip_runtime.h>\n#include "kernels.h"\n#include "shape.h"\n'
+        'extern "C" int line() { return LINE; }\n'
+        "hipError_t launch_attn(int, const AttnParams&, int, hipStream_t) { return hipSuccess; }\n")
+    if not os.path.exists(build_emu.CLANG):
+        pytest.skip("ROCm clang++ is needed for the host build")
+    first = build_emu.build(opt="-O0", csrc=str(csrc), out=str(tmp_path / "a"))
+    lifted = build_emu.build(opt="-O0", csrc=str(csrc), out=str(tmp_path / "b"), lift=[("LINE = 1", "LINE = 2")],
+                             base=str(tmp_path / "a"))
+    assert ctypes.CDLL(first).line() == 1 and ctypes.CDLL(lifted).line() == 2
