@@ -1032,13 +1032,15 @@ int tok_bv_rep(int D, int F) { return bv_rep(D, F); }
 int tok_mx_qkv_frags() { return Shape<256, 4, 4>::MX_QKV_FRAGS; }
 int tok_mx_scale_slot() { return Shape<256, 4, 4>::MX_SCALE_SLOT; }
 
+// Few tokens: the feature-split kernel (bit-identical), where this one's 128-token workgroups
+// would occupy few CUs. Post + QKV launch at d_model 256: 22 / 26 / 44 / 47 us for 78 / 507 / 780 /
+// 1014 token blocks against 46 / 48 / 49 / 50 here; at 1560 85 against 54 (the weights are streamed
+// once per two blocks there). At d_model 128, 688 blocks: 17 against 19 us; 1376: 23 against 20.
+static constexpr int64_t WIDE_MAX_BLOCKS = 1024;
+
 hipError_t launch_tok(int D, int F, int flags, const TokParams& p, int64_t n_tb, hipStream_t s) {
     if (n_tb <= 0) return hipSuccess;
-    // Few tokens: the feature-split kernel (bit-identical), where this one's 128-token workgroups
-    // would occupy few CUs. Post + QKV launch at d_model 256: 22 / 26 / 44 / 47 us for 78 / 507 / 780 /
-    // 1014 token blocks against 46 / 48 / 49 / 50 here; at 1560 85 against 54 (the weights are streamed
-    // once per two blocks there). At d_model 128, 688 blocks: 17 against 19 us; 1376: 23 against 20.
-    if (!(flags & TOK_MX) && n_tb <= 1024) return launch_wide(D, F, flags, p, n_tb, s);
+    if (!(flags & TOK_MX) && n_tb <= WIDE_MAX_BLOCKS) return launch_wide(D, F, flags, p, n_tb, s);
     if (D == 256 && F == 4 * D) return launch_tok_256_4(flags, p, n_tb, s);
     if (D == 256 && F == 5 * D) return launch_tok_256_5(flags, p, n_tb, s);
     if (D == 128 && F == 4 * D) return launch_tok_128_4(flags, p, n_tb, s);

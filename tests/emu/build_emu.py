@@ -21,6 +21,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
+sys.path.insert(0, ROOT)
+from paper_2601_09921_amd.build import PARTS  # noqa: E402
 CSRC = os.path.join(ROOT, "paper_2601_09921_amd", "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "_build")
@@ -156,15 +158,19 @@ def build(verbose: bool = False, opt: str = "-O2", csrc: str = CSRC, include: st
     flags = [opt, "-g", "-std=c++20", "-fPIC", "-w", "-I", HERE, "-I", src_out, "-x", "c++"]
     objs, procs = [], []
     for u in units + [os.path.join(HERE, "simt.cpp"), os.path.join(HERE, "units.cpp")]:
-        obj = os.path.join(out, os.path.basename(u) + ".o")
-        if base and os.path.basename(u) not in lifted:
-            objs.append(os.path.join(base, os.path.basename(u) + ".o"))
-            continue
-        cmd = [CLANG, *flags, "-c", u, "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True), u))
-        objs.append(obj)
+        name = os.path.basename(u)
+        macro, n = PARTS.get(name, ("", 1))   # the library's own parts, side by side
+        for i in range(n):
+            part = f"{name}.{i}.o" if macro else f"{name}.o"
+            if base and name not in lifted:
+                objs.append(os.path.join(base, part))
+                continue
+            obj = os.path.join(out, part)
+            cmd = [CLANG, *flags, *([f"-D{macro}={i}"] if macro else []), "-c", u, "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            procs.append((subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True), u))
+            objs.append(obj)
     for p, u in procs:
         log, _ = p.communicate()
         if p.returncode != 0:

@@ -18,6 +18,7 @@ def load(path: str) -> ctypes.CDLL:
     lib.emu_malloc.restype, lib.emu_malloc.argtypes = ctypes.c_void_p, [ctypes.c_size_t]
     lib.emu_free.restype, lib.emu_free.argtypes = None, [ctypes.c_void_p]
     lib.emu_errors.restype, lib.emu_errors.argtypes = ctypes.c_int, []
+    lib.emu_launches.restype, lib.emu_launches.argtypes = ctypes.c_int, [ctypes.c_char_p]
     return lib
 
 

@@ -64,6 +64,7 @@ int g_errors = 0;
 hipError_t g_last = hipSuccess;
 const char* g_what = "";               // the running launch
 uint64_t g_launch_no = 0;
+std::map<std::string, int> g_launches;   // per kernel name, without template arguments
 void* g_sched_sp = nullptr;
 Body g_body = nullptr;
 void* g_ctx = nullptr;
@@ -243,6 +244,7 @@ void run_grid(const char* what, dim3 grid, dim3 block, size_t smem, Body body, v
     install_handler();
     if (g_trace < 0) g_trace = std::getenv("EMU_TRACE") != nullptr;
     ++g_launch_no;
+    ++g_launches[std::string(what, std::strcspn(what, "<"))];
     g_what = what;
     if (g_trace) fprintf(stderr, "emu launch #%llu %s grid %u block %u smem %zu\n", (unsigned long long)g_launch_no,
                          what, grid.x, block.x, smem);
@@ -404,6 +406,7 @@ void* emu_malloc(size_t bytes) {
 }
 void emu_free(void* p) { (void)hipFree(p); }
 int emu_errors(void) { return emu::errors(); }
+int emu_launches(const char* kernel) { return emu::g_launches[kernel]; }
 // The i-th live allocation (in address order): its pointer and size; returns 0 past the last.
 int emu_allocation(int i, void** ptr, size_t* bytes) {
     for (auto& kv : g_allocs)

@@ -12,7 +12,7 @@ issuing lane's vector-memory wait.
 Covered here:
   * the attention kernel alone against softmax attention on the same bf16 operands;
   * whole decodes against the fp64 oracle (stabilizer and grid token sets, dilated
-    convolutions at d_model 128);
+    convolutions at d_model 128), on the kernels for few windows and on those for large batches;
   * the replay of the one GPU memory fault recorded for this library: the dilated
     convolutions at bf16 d_model 256 (d = 11, 3 windows, 2 layers, dilations 1, 2, 4), whose
     launches -- conv_kernel<256> (four weight chunks per tap), the out-projection-only and the
@@ -49,6 +49,13 @@ def _stale(lib: str) -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _load(lib: str):
+    h = run_emu.load(lib)
+    h.emu_attention.restype = ctypes.c_int
+    h.emu_attention.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p] + [ctypes.c_int] * 5
+    return h
+
+
 @pytest.fixture(scope="module")
 def emu():
     if not os.path.exists(build_emu.CLANG):
@@ -56,10 +63,19 @@ def emu():
     lib = os.path.join(build_emu.OUT, "libpwdec_emu.so")
     if _stale(lib):
         lib = build_emu.build()
-    h = run_emu.load(lib)
-    h.emu_attention.restype = ctypes.c_int
-    h.emu_attention.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p] + [ctypes.c_int] * 5
-    return h
+    return _load(lib)
+
+
+@pytest.fixture(scope="module")
+def large(emu):
+    """The library as it runs large batches: every batch on the token kernel and on the attention with
+    one workgroup per item, where the library as it is takes the kernels for few windows."""
+    out = os.path.join(build_emu.OUT, "large")
+    lib = os.path.join(out, "libpwdec_emu.so")
+    if not os.path.exists(lib) or os.path.getmtime(lib) < os.path.getmtime(build_emu.LIB):
+        lib = build_emu.build(out=out, base=build_emu.OUT, lift=[
+            ("WIDE_MAX_BLOCKS = 1024;", "WIDE_MAX_BLOCKS = 0;"), ("if (parts >= 2)", "if (parts < 0)")])
+    return _load(lib)
 
 
 def test_translation_leaves_no_device_only_construct():
@@ -87,11 +103,12 @@ ATTN_CASES = [(8, 256, 8, "normal"), (24, 256, 8, "normal"), (80, 256, 8, "norma
 
 
 @pytest.mark.parametrize("N,D,H,scores", ATTN_CASES, ids=[f"N{c[0]}_D{c[1]}_H{c[2]}_{c[3]}" for c in ATTN_CASES])
-def test_attention_kernel_alone(emu, N, D, H, scores):
+def test_attention_kernel_alone(emu, large, N, D, H, scores):
     """One window: Q (pre-scaled by log2(e)/sqrt(dh)), K, V written in the Q/K/V projection's
     fragment layouts; the kernel's output against softmax attention in float64 on the same
-    bf16 values (heads of 16 run in pairs, 64 in two fragments; N = 80 and 120 run two and
-    two wavefronts with padding keys). The kernel exponentiates unshifted scores; "overflow"
+    bf16 values (heads of 16 run in pairs, 64 in two fragments; padding keys at N = 8, 24 and 120),
+    bit for bit the same with an item's query blocks over several workgroups (few items; two at
+    N = 120) and in one. The kernel exponentiates unshifted scores; "overflow"
     scales Q so that rows reach hundreds of log2 units (exp2 overflows to inf), "underflow"
     gives every head's Q and K opposite shared components so that every score is below -150
     (every exp2 underflows): both go through the running-maximum recomputation."""
@@ -129,6 +146,11 @@ def test_attention_kernel_alone(emu, N, D, H, scores):
     Y = y.get()
     qkv.free()
     y.free()
+    qkv, y = run_emu.Buf(large, buf), run_emu.Buf(large, np.zeros((nbw, ksd, 64, 8), np.uint16))
+    assert large.emu_attention(dh, qkv.ptr, y.ptr, N, npad, nbw, H, 1) == 0
+    assert np.array_equal(Y, y.get()) and large.emu_errors() == 0
+    qkv.free()
+    y.free()
     out = np.zeros((npad, D))
     for tb in range(nbw):
         for f in range(ksd):
@@ -162,31 +184,40 @@ def _case(d, W, B, D, L, H, r, dil=(), grid=False, seed_base=1100):
     (9, 9, 2, 256, 1, 8, 4, ()),            # two attention wavefronts per item
     (5, 10, 6, 128, 2, 8, 4, (1, 2, 4)),    # dilated convolutions at d_model 128 (green on the GPU)
 ])
-def test_decode_matches_oracle(emu, d, W, B, D, L, H, r, dil):
+def test_decode_matches_oracle(emu, large, d, W, B, D, L, H, r, dil):
     wl, w, meas, types = _case(d, W, B, D, L, H, r, dil)
-    logits, bits, rc = run_emu.decode(emu, wl, w, meas, types)
-    o, _ = O.forward_windows(meas, types, w, d, H, grid=wl.grid)
-    assert rc == 0 and emu.emu_errors() == 0
-    assert np.abs(logits - o).max() <= BF16_ATOL
-    assert np.array_equal(bits, (logits > 0).astype(np.uint8))
+    _matches(emu, large, wl, w, meas, types)
 
 
-def test_replay_of_the_recorded_gpu_fault(emu):
+def _matches(emu, large, wl, w, meas, types):
+    """Both builds within the bf16 tolerance of the oracle, bit for bit the same, no access out of
+    any allocation; each ran its own token kernel."""
+    o, _ = O.forward_windows(meas, types, w, wl.d, wl.H, grid=wl.grid)
+    outs = []
+    for lib, kernel, other in ((emu, "wide_kernel", "tok_kernel"), (large, "tok_kernel", "wide_kernel")):
+        before = {k: lib.emu_launches(k.encode()) for k in (kernel, other)}
+        logits, bits, rc = run_emu.decode(lib, wl, w, meas, types)
+        assert rc == 0 and lib.emu_errors() == 0
+        assert lib.emu_launches(kernel.encode()) > before[kernel] and lib.emu_launches(other.encode()) == before[other]
+        assert np.abs(logits - o).max() <= BF16_ATOL
+        assert np.array_equal(bits, (logits > 0).astype(np.uint8))
+        outs.append(logits)
+    assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+
+
+def test_replay_of_the_recorded_gpu_fault(emu, large):
     """The configuration whose first GPU run ended in a memory fault: dilated convolutions at
     bf16 d_model 256, d = 11 on the (d+1)^2 grid, 3 windows, 2 layers, dilations 1, 2, 4, feed-
     forward 4x. Every launch of a round -- attention, the out-projection-only token kernel
     (which writes the convolutions' input G), three conv_kernel<256> units with four weight
     chunks per tap, and the feed-forward-only token kernels with the next round's embedding --
-    runs here on the CPU with every allocation fenced. One round's launches use the same
+    runs here on the CPU with every allocation fenced: on tok_kernel, as the recorded run, and on the
+    kernel that takes such a batch now. One round's launches use the same
     addresses in every round, so the window is cut to its core (11 rounds) to keep the CPU
     time down; the batch, layers, dilations and widths are the recorded ones. Result: no
     access outside any allocation, no LDS error, and logits within the bf16 tolerance of the
     oracle."""
-    wl, w, meas, types = _case(11, 11, 3, 256, 2, 8, 4, (1, 2, 4))
-    logits, bits, rc = run_emu.decode(emu, wl, w, meas, types)
-    o, _ = O.forward_windows(meas, types, w, 11, 8, grid=True)
-    assert rc == 0 and emu.emu_errors() == 0
-    assert np.abs(logits - o).max() <= BF16_ATOL
+    _matches(emu, large, *_case(11, 11, 3, 256, 2, 8, 4, (1, 2, 4)))
 
 
 def test_a_lifted_header_reaches_every_unit(tmp_path):
