@@ -76,14 +76,15 @@ PWD_DEV void sched_pipeline_pairs() {
     __builtin_amdgcn_sched_group_barrier(0x008, TAIL, 0);
 }
 
-// LayerNorm statistics of a token block held as C fragments (biased variance, two passes), and
-// their application to one value.
-template <int RT>
-PWD_DEV void ln_stats(const f32x4 (&x)[RT], float eps, float& mean, float& rstd) {
+// LayerNorm statistics of a token block held as C fragments at(0) .. at(RT - 1) (biased variance, two
+// passes), and their application to one value. (Fragments by accessor: copied out of a [RT][TB]
+// array first, the d_model-128 token kernels grew by 60 instructions.)
+template <int RT, class At>
+PWD_DEV void ln_stats(const At& at, float eps, float& mean, float& rstd) {
     constexpr float inv_d = 1.0f / (RT * 16);
     float s = 0.f;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) s += (x[rt][0] + x[rt][1]) + (x[rt][2] + x[rt][3]);
+    for (int rt = 0; rt < RT; ++rt) s += (at(rt)[0] + at(rt)[1]) + (at(rt)[2] + at(rt)[3]);
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
     mean = s * inv_d;
@@ -92,7 +93,7 @@ PWD_DEV void ln_stats(const f32x4 (&x)[RT], float eps, float& mean, float& rstd)
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float c = x[rt][i] - mean;
+            const float c = at(rt)[i] - mean;
             v += c * c;
         }
     v += __shfl_xor(v, 16);
@@ -108,11 +109,8 @@ template <int RT, int TB>
 PWD_DEV void layer_norm(f32x4 (&x)[RT][TB], const float* gamma, const float* beta, float eps, int g) {
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
-        f32x4 y[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) y[rt] = x[rt][b];
         float mean, rstd;
-        ln_stats<RT>(y, eps, mean, rstd);
+        ln_stats<RT>([&](int rt) -> const f32x4& { return x[rt][b]; }, eps, mean, rstd);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const f32x4 gm = ld4(gamma + rt * 16 + 4 * g);

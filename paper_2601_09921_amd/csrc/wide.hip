@@ -143,7 +143,7 @@ __global__ __launch_bounds__(D * 2, 2) void wide_kernel(TokParams p) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) v[rt] = ld4(xs + ((wave * RT + rt) * 64 + lane) * 4);
             float mean, rstd;
-            ln_stats<RT>(v, p.eps, mean, rstd);
+            ln_stats<RT>([&](int rt) -> const f32x4& { return v[rt]; }, p.eps, mean, rstd);
             stat[wave][0][lane] = mean;
             stat[wave][1][lane] = rstd;
         }
