@@ -400,7 +400,7 @@ PWD_DEV void attn_passes(const AttnShape& sh, const AttnItem& it, int qbeg, int 
     if (qend - qb == 1) run(std::integral_constant<int, 1>{}, qb);
 }
 
-// One workgroup per (window, head); K/V stay in LDS for the whole item. Workgroups of up to 4
+// One workgroup per (window, head) or part of it; K/V stay in LDS for the whole item. Workgroups of up to 4
 // wavefronts share a CU (as many as their tiles fit in LDS); 8 wavefronts (tiles above 80 KB)
 // keep two per SIMD on their own.
 // Heads of 16 share their K/V fragments with the neighbouring head, so a workgroup stages
@@ -408,7 +408,10 @@ PWD_DEV void attn_passes(const AttnShape& sh, const AttnItem& it, int qbeg, int 
 template <int DH>
 constexpr int heads_per_item() { return DH == 16 ? 2 : 1; }
 
-template <int DH, int WAVES>
+// SPLIT: an item's query blocks over p.parts workgroups. (A kernel of its own: with the two divisions
+// of its shares in the others, the launch over 1024 windows of 8 blocks, heads of 16, took 50.9
+// instead of 49.8 us.)
+template <int DH, int WAVES, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(AttnParams p) {
     constexpr int NF = Frag<DH>::NF, QM = Frag<DH>::QMAX;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -418,14 +421,18 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(At
     uint16_t* ks = reinterpret_cast<uint16_t*>(smem);   // [nbw][NF][512]: K fragments
     uint16_t* vs = ks + (size_t)nbw * NF * 512;          // [nbw + 1][NF][512]: V tiles, + a zero block
     constexpr int HPI = heads_per_item<DH>();
-    const int item = blockIdx.x / p.parts, part = blockIdx.x - item * p.parts;
+    int item = blockIdx.x, share = wave, shares = WAVES;
+    if constexpr (SPLIT) {
+        item = blockIdx.x / p.parts;
+        share += (blockIdx.x - item * p.parts) * WAVES;
+        shares *= p.parts;
+    }
     AttnItem it = make_item<DH>(p, sh, item * HPI);   // the pair's first head
     it.ks = ks;
     it.vs = vs;
 
     // Each wavefront owns a contiguous share of the item's query blocks; Q of its first pass is
     // loaded before the K/V staging, so its latency overlaps the staging.
-    const int share = part * WAVES + wave, shares = p.parts * WAVES;
     const int qbeg = share * nbw / shares, qend = (share + 1) * nbw / shares;
     u16x8 qnext[QM][NF];
     if (qbeg < qend) load_q<NF, QM>(sh, it.q0, qbeg, qend, lane, qnext);
@@ -449,14 +456,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(At
     }
 }
 
-template <int DH, int WAVES>
+template <int DH, int WAVES, bool SPLIT = false>
 hipError_t launch_shape(AttnParams p, int nwin, int parts, hipStream_t s) {
     p.parts = parts;
     const size_t smem = attn_smem_bytes(DH, p.Npad, p.nbw);
-    hipError_t e = hipFuncSetAttribute((const void*)attn_kernel<DH, WAVES>,
+    hipError_t e = hipFuncSetAttribute((const void*)attn_kernel<DH, WAVES, SPLIT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    attn_kernel<DH, WAVES><<<dim3((unsigned)nwin * p.H / heads_per_item<DH>() * parts), dim3(WAVES * 64), smem, s>>>(p);
+    attn_kernel<DH, WAVES, SPLIT><<<dim3((unsigned)nwin * p.H / heads_per_item<DH>() * parts), dim3(WAVES * 64), smem, s>>>(p);
     return hipGetLastError();
 }
 
@@ -482,7 +489,7 @@ hipError_t launch_dh(const AttnParams& p, int nwin, hipStream_t s) {
     const int items = nwin * p.H / heads_per_item<DH>();
     const int waves = fit < 2 ? 8 : 4, parts = std::min(256 * std::min(fit, 2) / items, p.nbw / waves);
     if (parts >= 2)
-        return waves == 8 ? launch_shape<DH, 8>(p, nwin, parts, s) : launch_shape<DH, 4>(p, nwin, parts, s);
+        return waves == 8 ? launch_shape<DH, 8, true>(p, nwin, parts, s) : launch_shape<DH, 4, true>(p, nwin, parts, s);
     if (p.nbw <= QM) return launch_shape<DH, 1>(p, nwin, 1, s);
     if (QM >= 4 && fit >= 8) return launch_shape<DH, 1>(p, nwin, 1, s);
     if (QM >= 4 ? fit >= 4 : p.nbw <= 2 * QM) return launch_shape<DH, 2>(p, nwin, 1, s);
