@@ -421,18 +421,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : 2) void attn_kernel(At
     uint16_t* ks = reinterpret_cast<uint16_t*>(smem);   // [nbw][NF][512]: K fragments
     uint16_t* vs = ks + (size_t)nbw * NF * 512;          // [nbw + 1][NF][512]: V tiles, + a zero block
     constexpr int HPI = heads_per_item<DH>();
-    int item = blockIdx.x, share = wave, shares = WAVES;
-    if constexpr (SPLIT) {
-        item = blockIdx.x / p.parts;
-        share += (blockIdx.x - item * p.parts) * WAVES;
-        shares *= p.parts;
-    }
+    const int parts = SPLIT ? p.parts : 1;
+    const int item = blockIdx.x / parts, part = blockIdx.x - item * parts;
     AttnItem it = make_item<DH>(p, sh, item * HPI);   // the pair's first head
     it.ks = ks;
     it.vs = vs;
 
     // Each wavefront owns a contiguous share of the item's query blocks; Q of its first pass is
     // loaded before the K/V staging, so its latency overlaps the staging.
+    const int share = part * WAVES + wave, shares = parts * WAVES;
     const int qbeg = share * nbw / shares, qend = (share + 1) * nbw / shares;
     u16x8 qnext[QM][NF];
     if (qbeg < qend) load_q<NF, QM>(sh, it.q0, qbeg, qend, lane, qnext);
@@ -483,12 +480,20 @@ hipError_t launch_dh(const AttnParams& p, int nwin, hipStream_t s) {
     const int fit = (int)(160 * 1024 / tile);
     // Few items: the query blocks of an item in several workgroups (each stages the item's K and V
     // again) of four wavefronts, eight where a tile fills a CU, until every CU has as many
-    // workgroups as it keeps (two; one) or a wavefront has a single block. d25, 64 items: 11.5
-    // against 19.4 us in one workgroup per item; 120 tokens, 224 items: 7.1 against 9.4. From half
-    // as many items on, one workgroup per item is as fast (d25, 416 items: 38.0 against 37.8).
+    // workgroups as it keeps (two; one) or a wavefront has a single block. 64 items of 39 blocks: 14.1
+    // against 20.5 us in one workgroup per item; 224 items of 8 blocks: 7.0 against 9.8.
+    // Two parts where two workgroups share a CU (from 171 items on) leave a CU a whole item and stage
+    // it twice. That pays where the whole-item workgroup has one or two wavefronts (176 items of 14
+    // blocks 8.7 against 11.3 us, 256 of 18 blocks 11.9 and 14.6), with two heads per staged tile (256
+    // items of 28 blocks, heads of 16: 23.9 and 25.9) and for short items of heads of 64 (192 of 11 blocks:
+    // 10.7 and 10.8), but not where it has four wavefronts anyway: heads of 32, 256 items of 23 blocks
+    // 15.1 against 13.4, of 39 blocks 26.3 and 24.6; heads of 64, of 18 blocks 17.3 and 16.1. There three
+    // parts are the fewest (160 items of 23, 28, 33, 39 blocks: 11.8, 15.8, 17.8, 20.6 against 12.3, 15.3,
+    // 18.7, 21.7 us).
     const int items = nwin * p.H / heads_per_item<DH>();
     const int waves = fit < 2 ? 8 : 4, parts = std::min(256 * std::min(fit, 2) / items, p.nbw / waves);
-    if (parts >= 2)
+    const bool four_waves_long = DH == 32 ? fit >= 2 && fit < 4 : DH == 64 && fit == 2;
+    if (parts >= (four_waves_long ? 3 : 2))
         return waves == 8 ? launch_shape<DH, 8, true>(p, nwin, parts, s) : launch_shape<DH, 4, true>(p, nwin, parts, s);
     if (p.nbw <= QM) return launch_shape<DH, 1>(p, nwin, 1, s);
     if (QM >= 4 && fit >= 8) return launch_shape<DH, 1>(p, nwin, 1, s);

@@ -74,7 +74,7 @@ def large(emu):
     lib = os.path.join(out, "libpwdec_emu.so")
     if not os.path.exists(lib) or os.path.getmtime(lib) < os.path.getmtime(build_emu.LIB):
         lib = build_emu.build(out=out, base=build_emu.OUT, lift=[
-            ("WIDE_MAX_BLOCKS = 1024;", "WIDE_MAX_BLOCKS = 0;"), ("if (parts >= 2)", "if (parts < 0)")])
+            ("WIDE_MAX_BLOCKS = 1024;", "WIDE_MAX_BLOCKS = 0;"), ("if (parts >= (four_waves_long ? 3 : 2))", "if (parts < 0)")])
     return _load(lib)
 
 

@@ -22,6 +22,9 @@ CASES = [
     ((13, 13, 128, 1, 8, 4, False, True, (), 0), 95, (1, 23, 24, 93)),              # heads of 16, 11 blocks
     ((25, 25, 128, 1, 8, 5, True, False, (), 0), 25, (1, 3, 7, 23)),                # tile of a whole CU's LDS
     ((7, 8, 128, 2, 8, 4, False, False, (), pwdec.SCHEDULE_LAYERS), 345, (1, 85, 86, 341)),
+    # on either side of the attention's line (168 and 176 items; 168 and 172)
+    ((19, 19, 256, 1, 8, 4, False, False, (), 0), 45, (1, 21, 22, 32, 44)),         # 23 blocks, heads of 32
+    ((17, 17, 256, 1, 4, 4, False, False, (), 0), 57, (1, 32, 42, 43, 56)),         # 18 blocks, heads of 64
     # d_model 256, 9 blocks a window: the embedder block and the parts around the convolutions
     ((11, 11, 256, 2, 8, 4, True, True, (1, 2, 4), 0), 115, (1, 2, 57, 113)),
     ((11, 11, 256, 1, 4, 5, True, True, (2, 1, 3), 0), 114, (1, 29, 113)),
