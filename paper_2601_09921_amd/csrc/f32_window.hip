@@ -108,10 +108,27 @@ PWD_DEV void refill(f32x4& w, const float* base, int off) {
 }
 PWD_DEV void refill(f32x4&, std::nullptr_t, int) {}
 
-// Wavefronts per SIMD: at d_model 32 and up to 24 tokens four (128 registers, a few spilled) let
-// four workgroups share a CU: 437 against 477 us for the 1000 windows above with three.
+// Wavefronts per SIMD that the registers are limited for (128, 168 or 256), at d_model 32 and 2 layers,
+// 4096 windows (and 64) with four / three / two, us:
+//     tokens, F/D   four          three         two
+//     8, 5          326 (55)      347 (49)      345 (48)
+//     16, 4         397 (59)      421 (55)      420 (56)
+//     16, 5         467 (75)      490 (70)      483 (64)
+//     24, 4         1090 (153)    1123 (136)    1086 (128)
+//     24, 5         1431 (204)    1291 (161)    1227 (144)
+//     36, 4         2206 (249)    1704 (203)    2011 (197)
+//     36, 5         3110 (294)    2415 (246)    2312 (231)
+// (8, 4 fits 128 registers.) Four cost spills, 40 registers at 24 tokens and F = 4 D, but let four
+// workgroups share a CU, which is a whole batch of 1000 windows at once: 437 against 477 us with three for
+// the 15 rounds above. At 24 tokens and F = 5 D, and from 25 tokens on, the spills cost more than that. At
+// F = 5 D two wavefronts give the better code (24 tokens: 163 registers, so three still fit); at 36
+// tokens and F = 4 D they leave too few workgroups. At d_model 16 the choice changes less than 3 %, but
+// for 64 tokens and F = 5 D (1617, 1536, 1508 us).
 template <int D, int MR, int NT>
-__global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (D == 64 ? 2 : NT + MR <= 7 ? 4 : 3)) void f32_window_kernel(F32Params p) {
+constexpr int f32_waves() { return D == 64 ? 2 : NT + MR <= 7 ? 4 : MR == 4 ? 3 : 2; }
+
+template <int D, int MR, int NT>
+__global__ __launch_bounds__((F32Shape<D, MR, NT>::THREADS), (f32_waves<D, MR, NT>())) void f32_window_kernel(F32Params p) {
     using S = F32Shape<D, MR, NT>;
     using V = F32Vec<D>;
     constexpr int WAVES = S::WAVES, KP = S::KP, TQ = S::TQ, KA = S::KA, NP = S::NP, NKB = S::NKB;

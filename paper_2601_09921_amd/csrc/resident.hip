@@ -36,11 +36,12 @@
 namespace {
 
 constexpr int RWAVES = 4;          // wavefronts, i.e. windows, per workgroup
-// Up to here resident_split.hip takes the batch: two of its passes over the CUs (one workgroup per
-// window, one on a CU at a time) still beat this kernel's one. Measured at 512 windows, L = 3, here
-// and there: 48 tokens, 14 rounds 1073 and 782 us; 64 tokens 1670 and 984; 24 tokens, 10 rounds 576
-// and 438; 8 tokens, 6 rounds 213 and 168. Three passes do not, except at 64 tokens: 768 windows 1115
-// and 1198, 1708 and 1666, 595 and 693, 224 and 272 (there with its first loads, 5 % slower).
+// Up to here resident_split.hip takes the batch. Two of its workgroups (one per window) share a CU at
+// one token block, at two to four blocks a CU holds one: 512 windows are one or two of its passes
+// over the CUs, and still beat this kernel's one. Measured at 512 windows, L = 3, here and there: 48
+// tokens, 14 rounds 1051 and 764 us; 64 tokens 1659 and 962; 24 tokens, 10 rounds 568 and 431; 8 tokens, 6
+// rounds 222 and 170. Another pass does not, except at 64 tokens: 640 windows 1074 and 1078, 1658 and
+// 1348, 586 and 606, 227 and 240.
 constexpr int SPLIT_MAX_WINDOWS = 512;
 constexpr int RLA = 8;             // fragment reads in flight ahead of their MFMAs (8: 8% faster than 4 at d7)
 

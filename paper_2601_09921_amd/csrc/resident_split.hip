@@ -14,9 +14,10 @@
 //
 // What bounds it is the chain of stages: eight exchanges with a barrier per layer and one wavefront
 // per SIMD, so attention, LayerNorms and the waits at barriers are exposed; the weights themselves,
-// 384 KB a layer at the CU's 64 bytes per cycle, are 2.6 us of the 8.4 us a layer takes at 48 tokens
-// (a ring of 8, 16, 24 or 32 fragments: 350, 354, 357, 357 us). 22 windows of 48 tokens, 14 rounds
-// of 3 layers: 1024 us (resident_kernel) to 354 us; 256 windows 1037 to 410 us.
+// 384 KB a layer at the CU's 64 bytes per cycle, are 2.6 us of the 8.3 us a layer takes at 48 tokens
+// (a ring of 8, 16, 24 or 32 fragments: 350, 354, 357, 357 us; 8 is also no slower at 8, 24 and 64
+// tokens, from 1 to 768 windows). 22 windows of 48 tokens, 14 rounds of 3 layers: 1024 us
+// (resident_kernel) to 350 us; 256 windows 1037 to 400 us.
 //
 // Bit for bit the results of resident_kernel (a window's result does not depend on the batch it
 // is in): the same stream, every output element accumulated over k in the same order in one
@@ -30,15 +31,13 @@
 namespace {
 
 constexpr int SWAVES = RKS;        // wavefronts of a window: one per 32-feature group
-// weight fragments in flight per wavefront: what four blocks leave of the register file
-template <int TB>
-constexpr int SRING_OF = TB < 4 ? 16 : 8;
+constexpr int SRING = 8;           // weight fragments in flight per wavefront
 
 template <int TB, int DH>
 __global__ __launch_bounds__(SWAVES * 64, 1) void resident_split_kernel(ResidentParams p) {
     using S = RShape<4>;
     using V = RVec<4>;
-    constexpr int FKS = S::F / 32, SRING = SRING_OF<TB>;   // hidden k-steps
+    constexpr int FKS = S::F / 32;   // hidden k-steps
     // a wavefront's fragments of one layer: [Q K V | Wo | W1 | W2]
     constexpr int N_WO = S::QKV_FRAGS, N_W1 = N_WO + 2 * RKS, N_W2 = N_W1 + 2 * FKS, N_END = N_W2 + 2 * FKS;
     static_assert(N_END % SRING == 0 && SRING <= N_END, "ring positions repeat every layer");
