@@ -32,7 +32,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 # flags>, flags POST=1, EMBED=2, QKV=4).
 STAGE_KERNELS = {
     "embed_qkv": "tok_kernel<256, 4, 6>",
-    "attention": "attn_kernel<32, 4>",
+    "attention": "attn_kernel<32, 4, false>",
     "post_qkv": "tok_kernel<256, 4, 5>",
     "post_embed_qkv": "tok_kernel<256, 4, 7>",
     "post": "tok_kernel<256, 4, 1>",

@@ -114,87 +114,87 @@ PWD_DEV bool in_range(const float (&sum)[NP], const f32x4 (&o)[NP]) {
 // accumulators over the window's TB blocks: y[qb] = O^T of query block qb as a B fragment.
 template <int TB, int DH>
 PWD_DEV void attend_group(const f32x4 (&q)[2][TB], const f32x4 (&k)[2][TB], const f32x4 (&v)[2][TB], bf16x8 (&y)[TB],
-                          float qscale, int ntok, int g, bf16x4 ones) {
-                    bf16x4 vt[2][TB];   // V^T A operands per 16-feature tile and key block
-    #pragma unroll
-                    for (int hh = 0; hh < 2; ++hh)
-    #pragma unroll
-                        for (int b = 0; b < TB; ++b) vt[hh][b] = to_b4(v[hh][b]);
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    if constexpr (DH == 16) {   // two heads per group: features 16 hh .. 16 hh + 15
-                        constexpr int NP = 2 * TB;   // pair p = query block p / 2, head p % 2
-                        bf16x4 q4[2][TB], k4[2][TB];
-    #pragma unroll
-                        for (int hh = 0; hh < 2; ++hh)
-    #pragma unroll
-                            for (int b = 0; b < TB; ++b) {
-                                q4[hh][b] = to_b4(q[hh][b] * qscale);
-                                k4[hh][b] = to_b4(k[hh][b]);
-                            }
-                        f32x4 o[NP];
-                        float inv[NP];
-                        auto attend = [&](auto shift) {
-                            f32x4 s[NP][TB];
-                            bf16x4 pb[NP][TB];
-                            float sum[NP];
-    #pragma unroll
-                            for (int pp = 0; pp < NP; ++pp)
-    #pragma unroll
-                                for (int kb = 0; kb < TB; ++kb) s[pp][kb] = mfma16x16x16(k4[pp % 2][kb], q4[pp % 2][pp / 2], zero);
-                            softmax_cols<decltype(shift)::value, NP, TB>(s, pb, sum, inv, ntok, g, ones);
-    #pragma unroll
-                            for (int pp = 0; pp < NP; ++pp) {
-                                o[pp] = zero;
-    #pragma unroll
-                                for (int kb = 0; kb < TB; ++kb) o[pp] = mfma16x16x16(vt[pp % 2][kb], pb[pp][kb], o[pp]);
-                            }
-                            return in_range<NP>(sum, o);
-                        };
-                        if (!attend(std::false_type{})) attend(std::true_type{});
-    #pragma unroll
-                        for (int qb = 0; qb < TB; ++qb) y[qb] = pack_b(o[2 * qb] * inv[2 * qb], o[2 * qb + 1] * inv[2 * qb + 1]);
-                    } else {   // one head of 32 features
-                        bf16x8 qf[TB], kf[TB];
-    #pragma unroll
-                        for (int b = 0; b < TB; ++b) {
-                            qf[b] = pack_b(q[0][b] * qscale, q[1][b] * qscale);
-                            kf[b] = pack_b(k[0][b], k[1][b]);
-                        }
-                        f32x4 o[TB][2];
-                        float inv[TB];
-                        auto attend = [&](auto shift) {
-                            f32x4 s[TB][TB];
-                            bf16x4 pb[TB][TB];
-                            float sum[TB];
-    #pragma unroll
-                            for (int qb = 0; qb < TB; ++qb)
-    #pragma unroll
-                                for (int kb = 0; kb < TB; ++kb) s[qb][kb] = mfma16x16x32(kf[kb], qf[qb], zero);
-                            softmax_cols<decltype(shift)::value, TB, TB>(s, pb, sum, inv, ntok, g, ones);
-    #pragma unroll
-                            for (int qb = 0; qb < TB; ++qb)
-    #pragma unroll
-                                for (int hh = 0; hh < 2; ++hh) {
-                                    o[qb][hh] = zero;
-    #pragma unroll
-                                    for (int kb = 0; kb < TB; ++kb) o[qb][hh] = mfma16x16x16(vt[hh][kb], pb[qb][kb], o[qb][hh]);
-                                }
-                            // both halves of each query block's output against its sum
-                            float sum2[2 * TB];
-                            f32x4 o2[2 * TB];
-    #pragma unroll
-                            for (int qb = 0; qb < TB; ++qb)
-    #pragma unroll
-                                for (int hh = 0; hh < 2; ++hh) {
-                                    sum2[2 * qb + hh] = sum[qb];
-                                    o2[2 * qb + hh] = o[qb][hh];
-                                }
-                            return in_range<2 * TB>(sum2, o2);
-                        };
-                        if (!attend(std::false_type{})) attend(std::true_type{});
-    #pragma unroll
-                        for (int qb = 0; qb < TB; ++qb) y[qb] = pack_b(o[qb][0] * inv[qb], o[qb][1] * inv[qb]);
-                    }
+          float qscale, int ntok, int g, bf16x4 ones) {
+    bf16x4 vt[2][TB];   // V^T A operands per 16-feature tile and key block
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int b = 0; b < TB; ++b) vt[hh][b] = to_b4(v[hh][b]);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (DH == 16) {   // two heads per group: features 16 hh .. 16 hh + 15
+        constexpr int NP = 2 * TB;   // pair p = query block p / 2, head p % 2
+        bf16x4 q4[2][TB], k4[2][TB];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                q4[hh][b] = to_b4(q[hh][b] * qscale);
+                k4[hh][b] = to_b4(k[hh][b]);
+            }
+        f32x4 o[NP];
+        float inv[NP];
+        auto attend = [&](auto shift) {
+            f32x4 s[NP][TB];
+            bf16x4 pb[NP][TB];
+            float sum[NP];
+#pragma unroll
+            for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+                for (int kb = 0; kb < TB; ++kb) s[pp][kb] = mfma16x16x16(k4[pp % 2][kb], q4[pp % 2][pp / 2], zero);
+            softmax_cols<decltype(shift)::value, NP, TB>(s, pb, sum, inv, ntok, g, ones);
+#pragma unroll
+            for (int pp = 0; pp < NP; ++pp) {
+                o[pp] = zero;
+#pragma unroll
+                for (int kb = 0; kb < TB; ++kb) o[pp] = mfma16x16x16(vt[pp % 2][kb], pb[pp][kb], o[pp]);
+            }
+            return in_range<NP>(sum, o);
+        };
+        if (!attend(std::false_type{})) attend(std::true_type{});
+#pragma unroll
+        for (int qb = 0; qb < TB; ++qb) y[qb] = pack_b(o[2 * qb] * inv[2 * qb], o[2 * qb + 1] * inv[2 * qb + 1]);
+    } else {   // one head of 32 features
+        bf16x8 qf[TB], kf[TB];
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            qf[b] = pack_b(q[0][b] * qscale, q[1][b] * qscale);
+            kf[b] = pack_b(k[0][b], k[1][b]);
+        }
+        f32x4 o[TB][2];
+        float inv[TB];
+        auto attend = [&](auto shift) {
+            f32x4 s[TB][TB];
+            bf16x4 pb[TB][TB];
+            float sum[TB];
+#pragma unroll
+            for (int qb = 0; qb < TB; ++qb)
+#pragma unroll
+                for (int kb = 0; kb < TB; ++kb) s[qb][kb] = mfma16x16x32(kf[kb], qf[qb], zero);
+            softmax_cols<decltype(shift)::value, TB, TB>(s, pb, sum, inv, ntok, g, ones);
+#pragma unroll
+            for (int qb = 0; qb < TB; ++qb)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    o[qb][hh] = zero;
+#pragma unroll
+                    for (int kb = 0; kb < TB; ++kb) o[qb][hh] = mfma16x16x16(vt[hh][kb], pb[qb][kb], o[qb][hh]);
+                }
+            // both halves of each query block's output against its sum
+            float sum2[2 * TB];
+            f32x4 o2[2 * TB];
+#pragma unroll
+            for (int qb = 0; qb < TB; ++qb)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    sum2[2 * qb + hh] = sum[qb];
+                    o2[2 * qb + hh] = o[qb][hh];
+                }
+            return in_range<2 * TB>(sum2, o2);
+        };
+        if (!attend(std::false_type{})) attend(std::true_type{});
+#pragma unroll
+        for (int qb = 0; qb < TB; ++qb) y[qb] = pack_b(o[qb][0] * inv[qb], o[qb][1] * inv[qb]);
+    }
 }
 
 }  // namespace

@@ -1034,8 +1034,14 @@ int tok_mx_scale_slot() { return Shape<256, 4, 4>::MX_SCALE_SLOT; }
 
 // Few tokens: the feature-split kernel (bit-identical), where this one's 128-token workgroups
 // would occupy few CUs. Post + QKV launch at d_model 256: 22 / 26 / 44 / 47 us for 78 / 507 / 780 /
-// 1014 token blocks against 46 / 48 / 49 / 50 here; at 1560 85 against 54 (the weights are streamed
-// once per two blocks there). At d_model 128, 688 blocks: 17 against 19 us; 1376: 23 against 20.
+// 1014 token blocks against 46 / 48 / 49 / 50 here; at 1280 and 1560 65 and 85 against 51 and 54 (the
+// weights are streamed once per two blocks there). At d_model 128, 512 blocks: 14 against 19 us; 1024: 20
+// and 21; 1280: 24 and 22. The line is the same for the other variants: at 1024 and 1280 blocks, d_model 256,
+// post + embedding + QKV 52 and 69 against 57 and 59 us, with the embedder block 58 and 80 against 62 and
+// 64; feed-forward + QKV 42 and 58 against 44 and 45; out-projection 17 and 21 against 18 and 19; F = 5 D 53 and
+// 72 against 55 and 57. (The embedding + QKV launch alone, one per decode, is up to 2 us slower there at d_model
+// 128.) The MXFP8 networks stay here at every size: their 8-bit fragments and scales come in another
+// stream order, which the feature-split kernel has no form for.
 static constexpr int64_t WIDE_MAX_BLOCKS = 1024;
 
 hipError_t launch_tok(int D, int F, int flags, const TokParams& p, int64_t n_tb, hipStream_t s) {
