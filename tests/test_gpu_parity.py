@@ -253,8 +253,11 @@ def test_attention_score_range(name, sign):
     block with a running maximum when its row sum or output leaves the normal fp32 range.
     With every score equal to +-(at least 184) log2 units, exp2 overflows to inf (sign +1) or
     underflows to 0 (sign -1) for every key: the results can only match the oracle's uniform
-    softmax through the running-maximum path (head sizes 16, 32 and 64)."""
+    softmax through the running-maximum path (head sizes 16, 32 and 64). A batch beyond the lines
+    of the few-window kernels (more than 512 windows; more than 256 attention items) runs the same
+    windows through the large-batch kernels' recomputation: bit for bit the same."""
     wl, B = RANGE_CASES[name]
+    large = 129 * B
     base = weights(name) if name in synth.WORKLOADS else synth.make_weights(wl, seed=5)
     w = constant_score_weights(wl, base, sign)
     meas, types = synth.make_windows(wl, B=B, seed=6)
@@ -271,8 +274,8 @@ def test_attention_score_range(name, sign):
         S = np.einsum("bnd,bmd->bnm", Q[:, :, sl], K[:, :, sl]) * math.log2(math.e) / math.sqrt(dh)
         assert np.all(S == S.flat[0]) and sign * S.flat[0] > 180, (h, S.flat[0])
     o_logits, _ = O.forward_windows(meas, types, w, wl.d, wl.H)
-    dec = pwdec.Decoder.from_workload(wl, w, max_windows=B)
-    # the layer-phased kernels, and for d7 the state-resident kernel (its own attention) too
+    dec = pwdec.Decoder.from_workload(wl, w, max_windows=large)
+    # the layer-phased kernels, and for d7 the state-resident ones (their own attention) too
     for schedule in [pwdec.SCHEDULE_LAYERS] + ([pwdec.SCHEDULE_RESIDENT] if name == "d7" else []):
         say(f"score range {name} sign={sign:+.0f} B={B} schedule={schedule}")
         dec.schedule(schedule)
@@ -283,6 +286,9 @@ def test_attention_score_range(name, sign):
         say(f"  max |gpu - oracle| = {err.max():.3e}")
         assert (err <= BF16_ATOL).all(), (logits, o_logits)
         check_bits(bits, o_logits)
+        many, _, rc = gpu_decode(dec, np.tile(meas, (129, 1, 1)), np.tile(types, 129))
+        assert rc == pwdec.PWD_OK
+        assert np.array_equal(many.view(np.uint32), np.tile(logits.view(np.uint32), 129))
     dec.close()
 
 

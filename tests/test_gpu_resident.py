@@ -1,8 +1,9 @@
 """GPU parity of the state-resident schedule (one launch for every round and layer, each window's
-state, Q, K and V in one wavefront's registers; Algorithm 1's recurrence carried on chip)
-against the fp64 oracle, through the C ABI: every window of small batches (all three window
-types, ragged last workgroup), the d7 workload's full batch sampled across it, zero syndromes,
-batch invariance, and agreement with the layer-phased schedule on the same decoder."""
+state on chip; Algorithm 1's recurrence carried there) against the fp64 oracle, through the C ABI:
+every window of small batches (all three window types; one workgroup per window), the d7 workload's
+full batch (one wavefront per window) sampled across it, zero syndromes, batch invariance, and
+agreement with the layer-phased schedule on the same decoder. The one-wavefront kernel at the other
+sizes is compared bit for bit with the one-workgroup kernel in test_gpu_resident_split.py."""
 import numpy as np
 import pytest
 
@@ -20,8 +21,7 @@ def need_gpu():
         pytest.skip("no GPU")
 
 
-# (d, W, B, H, L, grid): 1 to 4 token blocks per window, heads of 16 and 32, 1 to 4 layers,
-# batches that leave the last workgroup of four windows partly empty
+# (d, W, B, H, L, grid): 1 to 4 token blocks per window, heads of 16 and 32, 1 to 4 layers
 SHAPES = [
     (3, 6, 7, 8, 1, False),     # 8 tokens, one block
     (5, 10, 9, 4, 2, False),    # 24 tokens, two blocks, heads of 32
@@ -54,7 +54,7 @@ def test_resident_matches_oracle(d, W, B, H, L, grid):
     assert np.array_equal(bits, (logits > 0).astype(np.uint8))
     check_bits(bits, o)
     # batch invariance: a sub-batch starting at window 1 (every window moves to another
-    # wavefront and workgroup) gives the same logits bit for bit
+    # workgroup) gives the same logits bit for bit
     sub, _, _ = gpu_decode(dec, meas[1:], types[1:])
     assert np.array_equal(sub.view(np.uint32), logits[1:].view(np.uint32))
     # the layer-phased schedule of the same decoder agrees within the bf16 tolerance
