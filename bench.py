@@ -344,7 +344,8 @@ def paper_variant_measurement(wl, torch, pwdec, synth, dev_meas, dev_types):
 def input_stage_measurement(dec, wl, torch, dev_meas, dev_types, reps=5):
     """The input stage on its own: decoder_detection_events over the batch (packed measurement
     rounds in, packed detection events out; the same event_word the token kernel fuses),
-    timed with HIP events on the stream it runs on."""
+    timed with HIP events on the stream it runs on. The repetitions find the batch in the last-level
+    cache (66 MB at d = 25), so the rate is that cache's, not the HBM's it is set against."""
     B, W, words = wl.B, wl.W, wl.words
     events = torch.empty((B, W, words), dtype=torch.int32, device="cuda")
     stream = torch.cuda.current_stream()
